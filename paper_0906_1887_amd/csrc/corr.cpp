@@ -288,7 +288,7 @@ corr_status corr_internal_xengine(const corr_xpass* q) {
     e = corr::launch_xeng_mfma(a, q->elem, L.bt, q->stream);  // staged FP16 / FP8 rows and CI4 rows are aligned
   else if (c.engine == CORR_X_I8)
     e = aligned ? corr::launch_xeng_mfma(a, corr::kElemI8, L.bt, q->stream)
-                : corr::launch_xeng_i8(a, L.bt, false, q->stream);
+                : corr::launch_xeng_i8u(a, L.bt, q->stream);
   else
     e = corr::launch_xeng_f32(a, sb, L.bt, aligned, q->stream);
   if (e != hipSuccess) return CORR_E_HIP;

@@ -9,8 +9,8 @@ namespace corr {
 
 struct FArgs;
 
-// int8 MFMA X-engine; bt = 64 or 128; aligned: rows and base 16-byte aligned.
-hipError_t launch_xeng_i8(const XArgs& a, int bt, bool aligned, hipStream_t s);
+// int8 MFMA X-engine for rows of any (2-byte) alignment; bt = 64 or 128.
+hipError_t launch_xeng_i8u(const XArgs& a, int bt, hipStream_t s);
 // Matrix-core X-engine for 16-byte aligned rows; elem = kElemI8 / kElemF16 / kElemF8
 // (bt 64 or 128), or kElemCI4 / kElemF16Cvt / kElemF8Cvt (bt 128).
 hipError_t launch_xeng_mfma(const XArgs& a, int elem, int bt, hipStream_t s);
