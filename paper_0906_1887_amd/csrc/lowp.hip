@@ -14,9 +14,8 @@
 namespace corr {
 
 // Max |re|, |im| per channel (as float bits; non-negative floats order like
-// their bit patterns), one atomicMax per workgroup.  VEC: rows start 16-byte
-// aligned, so each lane reads two complex samples (one float4) at a time.
-template <bool VEC>
+// their bit patterns), one atomicMax per workgroup.  Each lane reads two
+// complex samples (16 bytes, any alignment) at a time.
 __global__ __launch_bounds__(256) void absmax_kernel(const float* __restrict__ x, int64_t n_in, int64_t n_t,
                                                       int64_t row_stride, int64_t rows_per_wg,
                                                       uint32_t* __restrict__ m_bits) {
@@ -27,25 +26,21 @@ __global__ __launch_bounds__(256) void absmax_kernel(const float* __restrict__ x
   float m = 0.f;
   for (int64_t r = r0; r < r1; ++r) {
     const float* row = x + ((ch * n_in + r) * row_stride) * 2;
-    if (VEC) {
-      const float4* rv = reinterpret_cast<const float4*>(row);
-      const int64_t nv = n_t / 2;
-      int64_t u = tid;
-      for (; u + 768 < nv; u += 1024) {
-        const float4 a = rv[u], b = rv[u + 256], c = rv[u + 512], d = rv[u + 768];
-        m = fmaxf(m, fmaxf(fmaxf(fmaxf(fabsf(a.x), fabsf(a.y)), fmaxf(fabsf(a.z), fabsf(a.w))),
-                           fmaxf(fmaxf(fabsf(b.x), fabsf(b.y)), fmaxf(fabsf(b.z), fabsf(b.w)))));
-        m = fmaxf(m, fmaxf(fmaxf(fmaxf(fabsf(c.x), fabsf(c.y)), fmaxf(fabsf(c.z), fabsf(c.w))),
-                           fmaxf(fmaxf(fabsf(d.x), fabsf(d.y)), fmaxf(fabsf(d.z), fabsf(d.w)))));
-      }
-      for (; u < nv; u += 256) {
-        const float4 a = rv[u];
-        m = fmaxf(m, fmaxf(fmaxf(fabsf(a.x), fabsf(a.y)), fmaxf(fabsf(a.z), fabsf(a.w))));
-      }
-      if ((n_t & 1) && tid == 0) m = fmaxf(m, fmaxf(fabsf(row[2 * n_t - 2]), fabsf(row[2 * n_t - 1])));
-    } else {
-      for (int64_t k = tid; k < 2 * n_t; k += 256) m = fmaxf(m, fabsf(row[k]));
+    const int64_t nv = n_t / 2;
+    int64_t u = tid;
+    for (; u + 768 < nv; u += 1024) {
+      const float4 a = load16_any<float4>(row + 4 * u), b = load16_any<float4>(row + 4 * (u + 256));
+      const float4 c = load16_any<float4>(row + 4 * (u + 512)), d = load16_any<float4>(row + 4 * (u + 768));
+      m = fmaxf(m, fmaxf(fmaxf(fmaxf(fabsf(a.x), fabsf(a.y)), fmaxf(fabsf(a.z), fabsf(a.w))),
+                         fmaxf(fmaxf(fabsf(b.x), fabsf(b.y)), fmaxf(fabsf(b.z), fabsf(b.w)))));
+      m = fmaxf(m, fmaxf(fmaxf(fmaxf(fabsf(c.x), fabsf(c.y)), fmaxf(fabsf(c.z), fabsf(c.w))),
+                         fmaxf(fmaxf(fabsf(d.x), fabsf(d.y)), fmaxf(fabsf(d.z), fabsf(d.w)))));
     }
+    for (; u < nv; u += 256) {
+      const float4 a = load16_any<float4>(row + 4 * u);
+      m = fmaxf(m, fmaxf(fmaxf(fabsf(a.x), fabsf(a.y)), fmaxf(fabsf(a.z), fabsf(a.w))));
+    }
+    if ((n_t & 1) && tid == 0) m = fmaxf(m, fmaxf(fabsf(row[2 * n_t - 2]), fabsf(row[2 * n_t - 1])));
   }
   __shared__ float red[256];
   red[tid] = m;
@@ -59,9 +54,8 @@ __global__ __launch_bounds__(256) void absmax_kernel(const float* __restrict__ x
 
 // One thread converts 4 complex samples of one row (grid: sample groups x
 // rows x channels).  Out rows have out_stride samples; FP16: 4 bytes per
-// sample, FP8: 2.  VEC: the row starts 16-byte aligned, so full groups are
-// read as two float4.
-template <int ELEM, bool VEC>
+// sample, FP8: 2.  Full groups are read as two 16-byte loads of any alignment.
+template <int ELEM>
 __global__ __launch_bounds__(256) void lowp_convert_kernel(const float* __restrict__ x, int64_t n_in, int64_t n_t,
                                                            int64_t row_stride, int64_t out_stride,
                                                            const uint32_t* __restrict__ m_bits, void* __restrict__ out,
@@ -77,9 +71,9 @@ __global__ __launch_bounds__(256) void lowp_convert_kernel(const float* __restri
   if (t0 >= n_t) return;
   const float* src = x + ((ch * n_in + r) * row_stride + t0) * 2;
   float v[8];
-  if (VEC && t0 + 4 <= n_t) {
-    const float4 a = reinterpret_cast<const float4*>(src)[0];
-    const float4 b = reinterpret_cast<const float4*>(src)[1];
+  if (t0 + 4 <= n_t) {
+    const float4 a = load16_any<float4>(src);
+    const float4 b = load16_any<float4>(src + 4);
     v[0] = a.x; v[1] = a.y; v[2] = a.z; v[3] = a.w;
     v[4] = b.x; v[5] = b.y; v[6] = b.z; v[7] = b.w;
   } else {
@@ -124,20 +118,15 @@ hipError_t launch_absmax(const float* x, int64_t n_ch, int64_t n_in, int64_t n_t
   if (n_ch > 65535) return hipErrorInvalidValue;
   hipError_t e = launch_fill_zero(m_bits, (n_ch * 4 + 15) / 16 * 16, s);
   if (e != hipSuccess || n_t <= 0) return e;
-  const bool vec = (reinterpret_cast<uintptr_t>(x) % 16 == 0) && (row_stride % 2 == 0);
   const int64_t rows_per_wg = 4;
   const dim3 g((unsigned)((n_in + rows_per_wg - 1) / rows_per_wg), (unsigned)n_ch);
-  if (vec)
-    hipLaunchKernelGGL(absmax_kernel<true>, g, dim3(256), 0, s, x, n_in, n_t, row_stride, rows_per_wg, m_bits);
-  else
-    hipLaunchKernelGGL(absmax_kernel<false>, g, dim3(256), 0, s, x, n_in, n_t, row_stride, rows_per_wg, m_bits);
+  hipLaunchKernelGGL(absmax_kernel, g, dim3(256), 0, s, x, n_in, n_t, row_stride, rows_per_wg, m_bits);
   return hipGetLastError();
 }
 
 hipError_t launch_lowp_stage(const LowpCall& c, hipStream_t s) {
   if (c.n_ch <= 0 || c.n_in <= 0 || c.n_t <= 0) return hipSuccess;
   if (c.n_ch > 65535 || c.n_in > 65535) return hipErrorInvalidValue;
-  const bool vec = (reinterpret_cast<uintptr_t>(c.x) % 16 == 0) && (c.row_stride % 2 == 0);
   if (c.elem == kElemF8) {
     const hipError_t e = launch_absmax(c.x, c.n_ch, c.n_in, c.n_t, c.row_stride, c.m_bits, s);
     if (e != hipSuccess) return e;
@@ -145,13 +134,13 @@ hipError_t launch_lowp_stage(const LowpCall& c, hipStream_t s) {
   const int64_t gx = ((c.n_t + 3) / 4 + 255) / 256;
   if (gx > 0x7FFFFFFF) return hipErrorInvalidValue;
   const dim3 g((unsigned)gx, (unsigned)c.n_in, (unsigned)c.n_ch);
-#define CORR_CONVERT(EL, V)                                                                                   \
-  hipLaunchKernelGGL((lowp_convert_kernel<EL, V>), g, dim3(256), 0, s, c.x, (int64_t)c.n_in, c.n_t, c.row_stride, \
+#define CORR_CONVERT(EL)                                                                                      \
+  hipLaunchKernelGGL((lowp_convert_kernel<EL>), g, dim3(256), 0, s, c.x, (int64_t)c.n_in, c.n_t, c.row_stride, \
                      c.out_stride, c.m_bits, c.out, c.inv_scale2)
   if (c.elem == kElemF16) {
-    if (vec) CORR_CONVERT(kElemF16, true); else CORR_CONVERT(kElemF16, false);
+    CORR_CONVERT(kElemF16);
   } else {
-    if (vec) CORR_CONVERT(kElemF8, true); else CORR_CONVERT(kElemF8, false);
+    CORR_CONVERT(kElemF8);
   }
 #undef CORR_CONVERT
   return hipGetLastError();

@@ -663,8 +663,6 @@ __device__ __forceinline__ void mfma_tile_128_cvt(const XArgs& a, int8_t* lds, i
   const int n_st = k1 > k0 ? (int)((k1 - k0 + kMKC - 1) / kMKC) : 0;
   const int64_t t0 = k0 / SB, t1 = k1 / SB;        // sample range of the pass
   const int64_t rsf = a.row_stride_b / 4;          // floats between rows (row_stride_b: float32 bytes)
-  // float4 loads when every row starts 16-byte aligned, else float2 loads
-  const bool a16 = ((reinterpret_cast<uintptr_t>(xc) | (uintptr_t)a.row_stride_b) & 15) == 0;
   float sc = 1.f;
   if constexpr (EKM == kElemF8) sc = e4m3_scale(__uint_as_float(a.m_bits[ch]));
 
@@ -699,13 +697,7 @@ __device__ __forceinline__ void mfma_tile_128_cvt(const XArgs& a, int8_t* lds, i
         const float* g = src[o][q] + t * 2;
         float4 v;
         if (t + 2 <= t1) {
-          if (a16) {
-            v = *reinterpret_cast<const float4*>(g);
-          } else {
-            const float2 u0 = reinterpret_cast<const float2*>(g)[0];
-            const float2 u1 = reinterpret_cast<const float2*>(g)[1];
-            v = make_float4(u0.x, u0.y, u1.x, u1.y);
-          }
+          v = load16_any<float4>(g);   // rows start 8-byte aligned
         } else {
           v = make_float4(0.f, 0.f, 0.f, 0.f);
           if (t < t1) {
