@@ -25,7 +25,9 @@
  *                one byte, re in the high nibble (1 B per sample).
  *   Memory       The caller owns every device buffer, including the workspace
  *                (size from corr_workspace_bytes); libcorr never allocates
- *                device memory.  The library owns only the host-side plan.
+ *                device memory.  The library owns only the host-side plan and,
+ *                from the first dump that waits on, one block of 4 MB of
+ *                pinned host memory per process (read-out results).
  *                All device work is queued on the stream given at creation;
  *                inputs must stay valid until the stream passes the call.
  *   Errors       Every call returns a corr_status; out-parameters are written
@@ -162,8 +164,8 @@ typedef struct {
 /* Bytes of device workspace a plan needs for `cfg`.  Host only.  The
  * workspace holds the plan's regions, the integration accumulator first (at
  * offset 0, [n_channels][P][2]), each region padded to 256 bytes and followed
- * by a 256-byte guard band; its last 256 bytes hold the guard check's result
- * (race and overrun detection: see corr_dump). */
+ * by a 256-byte guard band; its last 256 bytes are room for the guard check's
+ * result (race and overrun detection: see corr_dump). */
 corr_status corr_workspace_bytes(const corr_config *cfg, size_t *bytes);
 
 /* Validate `cfg`, carve the caller's workspace (device pointer, >= the size

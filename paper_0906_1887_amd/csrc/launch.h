@@ -22,7 +22,6 @@ int serve_blocks_per_cu();
 hipError_t launch_xeng_f32(const XArgs& a, int sample_bytes, int bt, bool aligned, hipStream_t s);
 hipError_t launch_reduce_splits(const void* part, int64_t n_pairs, int n_split, void* acc, int accumulate,
                                 bool is_int, hipStream_t s);
-hipError_t launch_fold_f64(double* L, const void* V, int64_t n_scalars, bool is_int, hipStream_t s);
 hipError_t launch_fill_zero(void* p, int64_t bytes, hipStream_t s);   // 16-byte aligned, bytes / 16 words
 hipError_t launch_fill_zero_bytes(void* p, int64_t bytes, hipStream_t s);
 
@@ -35,8 +34,31 @@ struct GuardList {
   int32_t n;
 };
 hipError_t launch_guard_fill(uint8_t* ws, const GuardList& g, hipStream_t s);
-// Writes the number of guard words that differ from the pattern to *bad.
-hipError_t launch_guard_check(const uint8_t* ws, const GuardList& g, uint32_t* bad, hipStream_t s);
+
+// What a dump queues, in one launch: the fold of the integration into the
+// long-run sum, the copy of either to dst, and the check of the guard bands
+// (the number of words that differ from the pattern goes to *bad, device or
+// mapped host memory).
+enum DumpMode {
+  kDumpCheck = 0,      // guard check only
+  kDumpCopy,           // dst = acc (n scalars of 4 bytes)
+  kDumpCopyLong,       // dst = L (n scalars of 8 bytes)
+  kDumpFold,           // L += acc
+  kDumpFoldCopy,       // L += acc, dst = acc
+  kDumpFoldCopyLong,   // L += acc, dst = L
+};
+struct DumpCall {
+  int mode;
+  bool is_int;             // acc is int32, else float32
+  const void* acc;
+  double* longrun;
+  void* dst;               // 4-byte aligned
+  int64_t n;               // scalars, a multiple of 2
+  const uint8_t* ws;       // guard bands' workspace; null: no check
+  GuardList guards;
+  uint32_t* bad;
+};
+hipError_t launch_dump(const DumpCall& c, hipStream_t s);
 
 struct FStageCall {
   const void* volt;        // real int8 (format 0), 16-bit 5+5 words (1) or 4+4 bytes (2)
