@@ -48,6 +48,7 @@ struct Layout {
   int max_split = 1;
   int bt = 128;
   int n_tiles = 0;
+  int64_t items = 0;                   // X-engine work items per K split
   int64_t ring_stride = 0;
   int64_t n_products = 0;
   corr::GuardList guards{};            // a guard band after each region
@@ -103,20 +104,34 @@ corr_status validate(const corr_config* c) {
   return CORR_OK;
 }
 
+// Largest K split of a pass with this many work items per split.
+int max_split_of(int64_t items) {
+  return items >= kTargetItems ? 1 : (int)std::min<int64_t>(kMaxSplit, (kTargetItems + items - 1) / items);
+}
+
 Layout layout_of(const corr_config* c) {
   Layout L;
   L.n_products = n_products(c->n_inputs);
-  // CI4 and the converting FP16/FP8 engines run 128-row tiles only
+  // CI4 and the converting FP16/FP8 engines run 128-row tiles only; the FP32
+  // engines 64-row tiles only (on the vector ALUs 128-row ones were level where
+  // they fill the GPU, and up to 1.4 times slower where they pad or leave CUs idle)
   const bool lowp_cvt = (c->engine == CORR_X_F16 || c->engine == CORR_X_F8) && c->ring_samples == 0;
-  // the FP32 matrix-core engine runs 64-row tiles only
-  L.bt = c->engine != CORR_X_FP32M && (c->n_inputs > 64 || c->sample_type == CORR_CI4 || lowp_cvt) ? 128 : 64;
+  const bool fp32 = c->engine == CORR_X_FP32 || c->engine == CORR_X_FP32M;
+  L.bt = !fp32 && (c->n_inputs > 64 || c->sample_type == CORR_CI4 || lowp_cvt) ? 128 : 64;
   const int64_t nb = (c->n_inputs + L.bt - 1) / L.bt;
   L.n_tiles = (int)(nb * (nb + 1) / 2);
-  const int64_t tiles_total = (int64_t)c->n_channels * L.n_tiles;
-  L.max_split = tiles_total >= kTargetItems
-                    ? 1
-                    : (int)std::min<int64_t>(kMaxSplit, (kTargetItems + tiles_total - 1) / tiles_total);
-  const size_t pair_bytes = 8;  // int2 (int8 engine) or float2 (others)
+  L.acc_bytes = (size_t)c->n_channels * L.n_products * 8;   // int2 (int8 engine) or float2 (others)
+  if (c->engine == CORR_X_FP32) {
+    // diagonal tiles in pairs; splits up to 8 items per CU while their partials
+    // fit corr_correlate_static's array (64 MiB are about 2000 items' products)
+    L.items = ((int64_t)c->n_channels * nb + 1) / 2 + (int64_t)c->n_channels * (L.n_tiles - nb);
+    const int64_t fit = (int64_t)(CORR_STATIC_SCRATCH_BYTES / L.acc_bytes);
+    L.max_split = (int)std::max<int64_t>(corr_internal_static_split(c, INT64_MAX / 2),
+                                         std::min<int64_t>({kMaxSplit, (2048 + L.items - 1) / L.items, fit}));
+  } else {
+    L.items = (int64_t)c->n_channels * L.n_tiles;
+    L.max_split = max_split_of(L.items);
+  }
   size_t off = 0;
   // each region is followed by a guard band (checked by corr_dump)
   auto end_region = [&](size_t bytes) {   // at most 9 regions, below kMaxGuards
@@ -125,7 +140,6 @@ Layout layout_of(const corr_config* c) {
     off += corr::kGuardBytes;
   };
   L.acc = off;
-  L.acc_bytes = (size_t)c->n_channels * L.n_products * pair_bytes;
   end_region(L.acc_bytes);
   if (c->fp64_longrun) {
     L.longrun = off;
@@ -303,12 +317,63 @@ corr_status xengine_pass(corr_plan* p, const void* x, int sb, int64_t n_samples,
 
 }  // namespace
 
-int corr_internal_split(const corr_config* c, int64_t n_samples) {
-  const Layout L = layout_of(c);
+namespace {
+
+// K splits of a pass, and the samples of each but the last.
+struct Split {
+  int n;
+  int64_t samples;
+};
+Split split_of(const corr_config& c, const Layout& L, int64_t n_samples) {
+  if (c.engine == CORR_X_FP32) {
+    // FP32 vector engine: a CU takes 1.44 us per item and stage of 16 samples
+    // whether 2, 3 or 4 items share it (256 channels of 64 inputs x 4000
+    // samples, one item on every second CU: 675 us; two per CU 802, three 1140,
+    // four 1437, eight 2880) and 2.66 us with one, so the pass takes as long
+    // as the CU with the most items; each item adds about two stages for its
+    // start and end, and a split the partials' way through memory.  A split's
+    // sums are one chain of FP32 additions, so there are never fewer splits
+    // than the matrix-core engines' tiles would give (4 instead of 11 for 128
+    // inputs x 96 channels x 2000 samples: 5 % faster, and 2.2 times further
+    // from the exact sums).
+    constexpr int64_t kF32Stage = 16;
+    const int64_t n_st = (n_samples + kF32Stage - 1) / kF32Stage;
+    const int s0 = corr_internal_static_split(&c, n_samples);
+    const size_t room = std::max<size_t>(CORR_STATIC_SCRATCH_BYTES, (size_t)s0 * L.acc_bytes);
+    Split best{1, 0};
+    double best_us = 0.0;
+    for (int s = s0; s <= L.max_split; ++s) {
+      const int64_t st = (n_st + s - 1) / s;
+      const int n = (int)((n_st + st - 1) / st);   // splits that hold samples
+      if (s > s0 && (st < 4 || (size_t)n * L.acc_bytes > room)) break;
+      const int64_t per_cu = (L.items * n + 255) / 256;
+      const double us = 1.44 * (per_cu == 1 ? 1.85 : (double)per_cu) * (double)(st + 2) +
+                        (n > 1 ? 5.0 + 2.0 * n * (double)L.acc_bytes / 4e6 : 0.0);
+      if (s == s0 || us < best_us) {
+        best_us = us;
+        best = Split{n, st * kF32Stage};
+      }
+    }
+    return best;
+  }
   const int64_t n_gran = (n_samples + kSplitGranule - 1) / kSplitGranule;
   // At least two granules (128 samples) per split: a 1000-sample integration
   // at N_I = 64 then takes 8 splits, 3 % faster than 4 splits of 256.
   int split = (int)std::min<int64_t>(L.max_split, std::max<int64_t>(1, n_gran / 2));
+  const int64_t gran_per_split = (n_gran + split - 1) / split;
+  return Split{(int)((n_gran + gran_per_split - 1) / gran_per_split), gran_per_split * kSplitGranule};
+}
+
+}  // namespace
+
+int corr_internal_split(const corr_config* c, int64_t n_samples) { return split_of(*c, layout_of(c), n_samples).n; }
+
+int corr_internal_static_split(const corr_config* c, int64_t n_samples) {
+  const int64_t bt = c->n_inputs > 64 || c->sample_type == CORR_CI4 ? 128 : 64;
+  const int64_t nb = (c->n_inputs + bt - 1) / bt;
+  const int64_t max = max_split_of((int64_t)c->n_channels * (nb * (nb + 1) / 2));
+  const int64_t n_gran = (n_samples + kSplitGranule - 1) / kSplitGranule;
+  const int64_t split = std::min<int64_t>(max, std::max<int64_t>(1, n_gran / 2));
   const int64_t gran_per_split = (n_gran + split - 1) / split;
   return (int)((n_gran + gran_per_split - 1) / gran_per_split);
 }
@@ -319,9 +384,8 @@ corr_status corr_internal_xengine(const corr_xpass* q) {
   const int64_t n_samples = q->n_samples;
   const int sb = q->sb;
   if (n_samples == 0) return CORR_OK;
-  const int64_t n_gran = (n_samples + kSplitGranule - 1) / kSplitGranule;
-  const int split = corr_internal_split(&c, n_samples);
-  const int64_t gran_per_split = (n_gran + split - 1) / split;
+  const Split sp = split_of(c, L, n_samples);
+  const int split = sp.n;
   if (split > 1 && (!q->part || q->part_bytes < (size_t)split * L.acc_bytes)) return CORR_E_WORKSPACE;
 
   corr::XArgs a;
@@ -333,14 +397,14 @@ corr_status corr_internal_xengine(const corr_xpass* q) {
   a.row_stride_b = q->row_stride * (cvt ? 8 : sb);
   a.ch_stride_b = (int64_t)c.n_inputs * a.row_stride_b;
   a.k_bytes = n_samples * sb;
-  a.k_split_bytes = gran_per_split * kSplitGranule * sb;
+  a.k_split_bytes = sp.samples * sb;
   a.n_products = L.n_products;
   a.n_in = c.n_inputs;
   a.n_ch = c.n_channels;
   a.n_tiles = L.n_tiles;
   a.n_split = split;
-  const int64_t items = (int64_t)c.n_channels * L.n_tiles * split;
-  if (items > 0x7FFFFFFFll / 2) return CORR_E_INVAL;
+  if ((int64_t)c.n_channels * L.n_tiles * split > 0x7FFFFFFFll / 2) return CORR_E_INVAL;
+  const int64_t items = L.items * split;
   a.n_items = (int32_t)items;
   a.per_xcd = (int32_t)((items + corr::kNumXcd - 1) / corr::kNumXcd);
   const bool direct = (split == 1);
@@ -361,7 +425,7 @@ corr_status corr_internal_xengine(const corr_xpass* q) {
     e = aligned ? corr::launch_xeng_mfma(a, corr::kElemI8, L.bt, q->stream)
                 : corr::launch_xeng_i8u(a, L.bt, q->stream);
   else
-    e = corr::launch_xeng_f32(a, sb, L.bt, aligned, q->stream);
+    e = corr::launch_xeng_f32(a, sb, q->stream);
   if (e != hipSuccess) return CORR_E_HIP;
   if (!direct) {
     e = corr::launch_reduce_splits(q->part, (int64_t)c.n_channels * L.n_products, split, q->acc, q->accumulate,

@@ -86,7 +86,8 @@ extern "C" corr_status corr_correlate_static(const corr_config* cfg, const void*
     const size_t acc_bytes = (size_t)cfg->n_channels * (size_t)P * 8;
     const int split = corr_internal_split(cfg, n_samples);
     const size_t part_bytes = split > 1 ? (size_t)split * acc_bytes : 0;
-    if (part_bytes > kScratchBytes) return CORR_E_WORKSPACE;
+    const int counted = corr_internal_static_split(cfg, n_samples);
+    if (part_bytes > kScratchBytes || (counted > 1 && (size_t)counted * acc_bytes > kScratchBytes)) return CORR_E_WORKSPACE;
 
     hipError_t e = hipSuccess;
     uint8_t* base = static_cast<uint8_t*>(scratch_ptr(&e));

@@ -42,3 +42,6 @@ struct corr_xpass {
 CORR_HIDDEN corr_status corr_internal_xengine(const corr_xpass* q);
 // K splits of a pass of n_samples for configuration c (1 = no partials).
 CORR_HIDDEN int corr_internal_split(const corr_config* c, int64_t n_samples);
+// K splits by which corr_correlate_static's limit counts: those of the
+// matrix-core engines' tiles (the FP32 engine's own split fits wherever these do).
+CORR_HIDDEN int corr_internal_static_split(const corr_config* c, int64_t n_samples);
