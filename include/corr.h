@@ -397,7 +397,7 @@ corr_status corr_dump_bytes(const corr_plan *plan, int32_t what, size_t *bytes);
  * stride) are correlated through a per-job plan on one of n_streams streams
  * instead.  A job whose footprint exceeds the whole arena is refused at
  * submission (CORR_E_WORKSPACE).  The scheduler allocates, besides its host
- * objects, 264 KB of pinned host memory (completion words and the staging of
+ * objects, about 200 KB of pinned host memory (completion words and the staging of
  * queue updates); no device memory.
  * ------------------------------------------------------------------------ */
 typedef struct corr_sched corr_sched;

@@ -18,6 +18,9 @@ hipError_t launch_xeng_mfma(const XArgs& a, int elem, int bt, hipStream_t s);
 // grid = workgroups.
 hipError_t launch_xeng_serve(const ServeQueue& q, int grid, hipStream_t s);
 int serve_blocks_per_cu();
+// Apply a queue update (u: device view) of n_jobs new jobs and a list of n_active slots.
+hipError_t launch_xeng_publish(const ServeUpdate* u, int n_jobs, int n_active, uint32_t version, const ServeQueue& q,
+                               hipStream_t s);
 // FP32 X-engine (64-row tiles), rows of any sample alignment; sample_bytes = 8 (complex float32) or 2 (complex int8).
 // n_items: per split, the pairs of diagonal tiles of all channels and the off-diagonal tiles.
 hipError_t launch_xeng_f32(const XArgs& a, int sample_bytes, hipStream_t s);

@@ -10,8 +10,9 @@
 //
 // Device queue (the batched path).  An admitted job is published in a slot
 // of a job queue in the arena's head: its pass (sample and result pointers,
-// shape) and the claim limit of its work items, one per (channel, 128-row
-// baseline tile).  A persistent serving grid (xeng_serve_kernel, as many
+// shape) and its number of work items, one per (channel, 128-row baseline
+// tile), under a new generation of the slot; the jobs admitted together are
+// published by one small kernel.  A persistent serving grid (xeng_serve_kernel, as many
 // workgroups as the GPU holds at once but kCopyReserve) runs while published
 // work remains.  Its workgroups claim items round robin over the listed jobs,
 // so jobs that arrive while others run are taken up by the grid already on
@@ -31,6 +32,7 @@
 // the per-job path instead: a corr_plan carved from the arena, the plan's
 // X-engine launch and a copy, on one of the scheduler's streams.
 #include <hip/hip_runtime.h>
+#include <sys/prctl.h>
 
 #include <algorithm>
 #include <atomic>
@@ -55,10 +57,11 @@ namespace {
 constexpr size_t kAlign = 256;
 constexpr double kMaxHeadWait = 0.020;   // s a blocked head job lets smaller jobs pass
 constexpr int kLookahead = 16;
-constexpr int kSlots = 64;               // jobs on the device queue at once
-constexpr int kStage = 512;              // pinned staging entries for queue updates
-constexpr size_t kStageBytes = 512;
+constexpr int kSlots = corr::kServeSlots;  // jobs on the device queue at once
+constexpr int kStage = 16;               // pinned staging entries for queue updates
+constexpr size_t kStageBytes = (sizeof(corr::ServeUpdate) + 255) / 256 * 256;
 constexpr double kIdleUs = 100.0;        // queue idle this long: the serving grid closes
+constexpr size_t kQueueHead = 36096;     // bytes of the arena's head that the queue takes (corr.h)
 constexpr int kMaxPolls = 1 << 18;       // bound on one serving workgroup's empty polls
 constexpr int kCopyStreams = 4;          // streams a large host copy is split over
 constexpr size_t kCopyPart = 32u << 20;  // at least this many bytes per part
@@ -85,7 +88,7 @@ struct Job {
   bool queued_path = true;             // device queue, else per-job plan
   int slot = -1;
   uint64_t items = 0;
-  uint64_t limit = 0;                  // claim limit of the job's items
+  corr::ServeJob sj{};                 // its pass, as published
   bool claimed_all = false;            // the device has claimed every item
   uint32_t flag_value = 0;
   corr_plan* plan = nullptr;
@@ -161,28 +164,24 @@ corr_config job_config(const corr_job_desc& d) {
 
 // Device-queue layout in the arena's head (byte offsets).
 struct QueueLayout {
-  size_t slots = 0, limit = 0, claim = 0, done = 0, active = 0, rr = 0, last_claim = 0, closing = 0, total = 0;
+  size_t slots = 0, claim = 0, done = 0, active = 0, last_claim = 0, closing = 0, total = 0;
 };
 QueueLayout queue_layout() {
   QueueLayout q;
   size_t off = 0;
   q.slots = off;
   off = align_up(off + kSlots * sizeof(corr::ServeJob));
-  q.limit = off;
-  off = align_up(off + kSlots * corr::kServeLine * 4);
   q.claim = off;
   off = align_up(off + kSlots * corr::kServeLine * 4);
   q.done = off;
   off = align_up(off + kSlots * corr::kServeLine * 4);
   q.active = off;
-  off = align_up(off + (kSlots + 1) * 4);
-  q.rr = off;
-  off = align_up(off + 128);
+  off = align_up(off + (2 * kSlots + 1) * 8);
   q.last_claim = off;
   off = align_up(off + 128);
   q.closing = off;
   off = align_up(off + 128);
-  q.total = off;
+  q.total = std::max(off, kQueueHead);
   return q;
 }
 
@@ -198,7 +197,7 @@ struct corr_sched {
   hipStream_t s_copy = nullptr;            // results to host destinations (and the completion callback)
   hipStream_t s_copy_x[kCopyStreams - 1] = {};  // further parts of large host copies
   hipEvent_t ev_copy_x[kCopyStreams - 1] = {};
-  hipEvent_t ev_pub = nullptr;             // after the latest queue update
+  hipEvent_t ev_pub = nullptr;             // after the latest queue update (one of stage_ev)
   hipEvent_t ev_grid[2] = {nullptr, nullptr};
   bool grid_alive[2] = {false, false};     // launched, completion not yet seen
   uint32_t grid_gen[2] = {0, 0};           // generation of the grid on each stream
@@ -211,13 +210,15 @@ struct corr_sched {
                                            // then the closed-grid generation
   uint32_t* d_flags = nullptr;             // their device view
   uint8_t* stage = nullptr;                // pinned host staging ring for queue updates
+  uint8_t* d_stage = nullptr;              // its device view
+  std::vector<Job*> batch;                 // admitted since the latest queue update
   hipEvent_t stage_ev[kStage] = {};
   bool stage_used[kStage] = {};
   int stage_next = 0;
-  uint64_t slot_limit[kSlots] = {};        // claim limit of each slot's latest job
+  uint32_t slot_gen[kSlots] = {};          // generation of each slot's latest job
   Job* slot_job[kSlots] = {};
   std::vector<int> free_slots;
-  bool active_dirty = false;
+  uint32_t list_version = 0;               // of the list of active slots
   uint32_t next_flag = 0;
   std::mutex mu;
   std::condition_variable cv;
@@ -252,37 +253,58 @@ void on_done(void* arg) {
   o->callbacks.fetch_sub(1);
 }
 
-// Copy `bytes` through a pinned staging entry (whose previous copy has
-// completed) to the arena at arena_off, on the control stream (lock held).
-hipError_t stage_copy(corr_sched* s, size_t arena_off, const void* src, size_t bytes) {
+// Publish the jobs of the batch and the list of slots holding jobs with
+// unclaimed items, through a pinned staging entry whose previous update has
+// been applied, by one kernel on the control stream (lock held).
+hipError_t publish(corr_sched* s) {
   const int k = s->stage_next;
   s->stage_next = (k + 1) % kStage;
   if (s->stage_used[k]) hipEventSynchronize(s->stage_ev[k]);
   s->stage_used[k] = true;
-  uint8_t* e = s->stage + (size_t)k * kStageBytes;
-  std::memcpy(e, src, bytes);
-  hipError_t r = hipMemcpyAsync(s->arena_base + arena_off, e, bytes, hipMemcpyHostToDevice, s->s_ctl);
-  if (r == hipSuccess) r = hipEventRecord(s->stage_ev[k], s->s_ctl);
-  return r;
-}
-
-// Publish the list of slots holding jobs with unclaimed items (lock held).
-hipError_t publish_active(corr_sched* s) {
-  int32_t list[kSlots + 1];
-  int n = 0;
-  for (int k = 0; k < kSlots; ++k) {
-    const Job* j = s->slot_job[k];
-    if (j && j->state.load() == kRunning && !j->claimed_all) list[1 + n++] = k;
+  static_assert(sizeof(corr::ServeUpdate) <= kStageBytes, "an update fits its staging entry");
+  corr::ServeUpdate& u = *reinterpret_cast<corr::ServeUpdate*>(s->stage + (size_t)k * kStageBytes);
+  for (size_t b = 0; b < s->batch.size(); ++b) {
+    u.slot[b] = s->batch[b]->slot;
+    u.job[b] = s->batch[b]->sj;
   }
-  list[0] = n;
-  s->active_dirty = false;
-  hipError_t r = stage_copy(s, s->ql.active, list, sizeof(int32_t) * (n + 1));
-  if (r == hipSuccess) r = hipEventRecord(s->ev_pub, s->s_ctl);
+  int n = 0;
+  for (int q = 0; q < kSlots; ++q) {
+    const Job* j = s->slot_job[q];
+    if (j && j->state.load() == kRunning && !j->claimed_all) {
+      u.active[2 * n] = corr::serve_entry(q, j->sj.x.n_items);
+      u.active[2 * n + 1] = j->sj.gen;
+      ++n;
+    }
+  }
+  const hipError_t r = corr::launch_xeng_publish(
+      reinterpret_cast<const corr::ServeUpdate*>(s->d_stage + (size_t)k * kStageBytes), (int)s->batch.size(), n,
+      ++s->list_version, s->q, s->s_ctl);   // one slot a job, so at most kSlots
+  if (r != hipSuccess) {
+    s->stage_used[k] = false;
+    return r;
+  }
+  s->ev_pub = s->stage_ev[k];
+  if (hipEventRecord(s->ev_pub, s->s_ctl) != hipSuccess) {   // wait for the update instead
+    hipStreamSynchronize(s->s_ctl);
+    s->stage_used[k] = false;
+    s->ev_pub = nullptr;
+  }
+  s->work_since_launch = true;
   return r;
 }
 
-// Admit one job on the device queue (lock held).
-corr_status launch_queued(corr_sched* s, Job* j) {
+// A job of the batch whose update was not launched (lock held).
+void fail_queued(corr_sched* s, Job* j, corr_status rc) {
+  j->status = rc;
+  s->slot_job[j->slot] = nullptr;
+  s->free_slots.push_back(j->slot);
+  j->t_done.store(now_s());
+  j->state.store(kDone);
+}
+
+// Admit one job on the device queue: queue its fill and add it to the batch
+// that the next update publishes (lock held).
+void launch_queued(corr_sched* s, Job* j) {
   const corr_job_desc& d = j->d;
   j->slot = s->free_slots.back();
   s->free_slots.pop_back();
@@ -300,7 +322,7 @@ corr_status launch_queued(corr_sched* s, Job* j) {
     d.fill(d.fill_user, j->id, const_cast<void*>(samples), d.n_channels, d.n_inputs, d.n_samples, stride,
            s->s_ctl);
   }
-  corr::ServeJob sj;
+  corr::ServeJob& sj = j->sj;
   std::memset(&sj, 0, sizeof(sj));
   const int64_t nb = (d.n_inputs + 127) / 128;
   corr::XArgs& a = sj.x;
@@ -321,18 +343,8 @@ corr_status launch_queued(corr_sched* s, Job* j) {
   if (j->flag_value == 0) j->flag_value = ++s->next_flag;
   sj.flag = s->d_flags + (size_t)j->slot * corr::kServeLine;
   sj.flag_value = j->flag_value;
-  sj.base = s->slot_limit[j->slot];
-  s->slot_limit[j->slot] += j->items;
-  const uint64_t lim = s->slot_limit[j->slot];
-  j->limit = lim;
-  // The job, then its claim limit (a grid claims an item only below the
-  // limit, so it sees the job -- and the fill before it -- first), then the
-  // list of active slots.
-  hipError_t r = stage_copy(s, s->ql.slots + (size_t)j->slot * sizeof(corr::ServeJob), &sj, sizeof(sj));
-  if (r == hipSuccess) r = stage_copy(s, s->ql.limit + (size_t)j->slot * corr::kServeLine * 4, &lim, sizeof(lim));
-  if (r == hipSuccess) r = publish_active(s);
-  s->work_since_launch = true;
-  return r == hipSuccess ? CORR_OK : CORR_E_HIP;
+  sj.gen = ++s->slot_gen[j->slot];
+  s->batch.push_back(j);
 }
 
 // Admit one job on the per-job path (lock held): carve its region, create its
@@ -394,7 +406,7 @@ void launch_grids(corr_sched* s) {
   if (free_g < 0) return;                                        // both streams hold closing grids
   corr::ServeQueue q = s->q;
   q.gen = s->next_gen + 1;
-  if (hipStreamWaitEvent(s->s_grid[free_g], s->ev_pub, 0) != hipSuccess) return;
+  if (s->ev_pub && hipStreamWaitEvent(s->s_grid[free_g], s->ev_pub, 0) != hipSuccess) return;
   if (corr::launch_xeng_serve(q, s->grid_cap, s->s_grid[free_g]) != hipSuccess) return;
   if (hipEventRecord(s->ev_grid[free_g], s->s_grid[free_g]) != hipSuccess) return;
   s->next_gen = q.gen;
@@ -422,11 +434,10 @@ void collect_queue(corr_sched* s) {
       const uint64_t c = __atomic_load_n(reinterpret_cast<const uint64_t*>(s->flags) +
                                              (size_t)j->slot * (corr::kServeLine / 2) + 1,
                                          __ATOMIC_ACQUIRE);
-      if (c == j->limit) {
-        // every item is claimed: list the job no more, so the grid's
-        // workgroups do not scan past it
+      if (c == j->sj.gen) {
+        // every item is claimed: the next update lists the job no more (until
+        // then each workgroup looks at it once and remembers)
         j->claimed_all = true;
-        s->active_dirty = true;
       }
     }
     const uint32_t f = __atomic_load_n(s->flags + (size_t)j->slot * corr::kServeLine, __ATOMIC_ACQUIRE);
@@ -435,7 +446,6 @@ void collect_queue(corr_sched* s) {
     j->n_out = j->d.n_samples;
     s->slot_job[j->slot] = nullptr;
     s->free_slots.push_back(j->slot);
-    s->active_dirty = true;
     if (j->d.dst_is_device) {
       j->t_done.store(j->t_device);
       j->state.store(kDone);
@@ -475,6 +485,9 @@ void collect_queue(corr_sched* s) {
 }
 
 void worker_loop(corr_sched* s) {
+  // The short waits below are this long, not longer by the default 50 us of
+  // timer slack.
+  (void)prctl(PR_SET_TIMERSLACK, 1000UL, 0UL, 0UL, 0UL);
   std::unique_lock<std::mutex> lk(s->mu);
   for (;;) {
     collect_queue(s);
@@ -504,15 +517,7 @@ void worker_loop(corr_sched* s) {
         j->off = off;
         s->pending.erase(s->pending.begin() + k);
         if (j->queued_path) {
-          const corr_status rc = launch_queued(s, j);
-          if (rc != CORR_OK) {
-            hipStreamSynchronize(s->s_ctl);
-            j->status = rc;
-            s->slot_job[j->slot] = nullptr;
-            s->free_slots.push_back(j->slot);
-            j->t_done.store(now_s());
-            j->state.store(kDone);
-          }
+          launch_queued(s, j);
         } else {
           launch_plan_job(s, j);
         }
@@ -520,7 +525,13 @@ void worker_loop(corr_sched* s) {
         break;
       }
     }
-    if (s->active_dirty) publish_active(s);
+    if (!s->batch.empty()) {
+      if (publish(s) != hipSuccess) {
+        hipStreamSynchronize(s->s_ctl);
+        for (Job* j : s->batch) fail_queued(s, j, CORR_E_HIP);
+      }
+      s->batch.clear();
+    }
     launch_grids(s);
     if (s->stop && s->pending.empty() && s->running.empty()) break;
     bool busy = s->work_since_launch || s->grid_alive[0] || s->grid_alive[1];
@@ -562,7 +573,7 @@ corr_status corr_sched_create(void* d_arena, size_t arena_bytes, int32_t n_strea
       ok = ok && hipStreamCreateWithFlags(&s->s_copy_x[k], hipStreamNonBlocking) == hipSuccess;
       ok = ok && hipEventCreateWithFlags(&s->ev_copy_x[k], hipEventDisableTiming) == hipSuccess;
     }
-    for (hipEvent_t* e : {&s->ev_pub, &s->ev_grid[0], &s->ev_grid[1]})
+    for (hipEvent_t* e : {&s->ev_grid[0], &s->ev_grid[1]})
       ok = ok && hipEventCreateWithFlags(e, hipEventDisableTiming) == hipSuccess;
     for (int k = 0; k < kStage && ok; ++k)
       ok = hipEventCreateWithFlags(&s->stage_ev[k], hipEventDisableTiming) == hipSuccess;
@@ -570,10 +581,11 @@ corr_status corr_sched_create(void* d_arena, size_t arena_bytes, int32_t n_strea
     // serving grids write, and the staging ring for queue updates.
     ok = ok && hipHostMalloc(reinterpret_cast<void**>(&s->flags), (kSlots + 1) * corr::kServeLine * 4,
                              hipHostMallocMapped) == hipSuccess;
-    ok = ok && hipHostMalloc(reinterpret_cast<void**>(&s->stage), kStage * kStageBytes, hipHostMallocDefault) ==
+    ok = ok && hipHostMalloc(reinterpret_cast<void**>(&s->stage), kStage * kStageBytes, hipHostMallocMapped) ==
                    hipSuccess;
     void* d_flags = nullptr;
     ok = ok && hipHostGetDevicePointer(&d_flags, s->flags, 0) == hipSuccess;
+    ok = ok && hipHostGetDevicePointer(reinterpret_cast<void**>(&s->d_stage), s->stage, 0) == hipSuccess;
     // The queue's words start at zero.
     ok = ok && corr::launch_fill_zero(s->arena_base, (int64_t)ql.total, s->s_ctl) == hipSuccess;
     ok = ok && hipStreamSynchronize(s->s_ctl) == hipSuccess;
@@ -589,17 +601,15 @@ corr_status corr_sched_create(void* d_arena, size_t arena_bytes, int32_t n_strea
         hipDeviceGetAttribute(&clock_khz, hipDeviceAttributeWallClockRate, dev) != hipSuccess)
       cus = 0;   // no serving grid: every job takes the per-job path
     s->grid_cap = std::max(0, corr::serve_blocks_per_cu() * cus - kCopyReserve);
-    s->q.slots = reinterpret_cast<const corr::ServeJob*>(s->arena_base + ql.slots);
-    s->q.limit = reinterpret_cast<const uint64_t*>(s->arena_base + ql.limit);
+    s->q.slots = reinterpret_cast<corr::ServeJob*>(s->arena_base + ql.slots);
     s->q.claim = reinterpret_cast<uint64_t*>(s->arena_base + ql.claim);
     s->q.done = reinterpret_cast<uint32_t*>(s->arena_base + ql.done);
-    s->q.active = reinterpret_cast<const int32_t*>(s->arena_base + ql.active);
+    s->q.active = reinterpret_cast<uint64_t*>(s->arena_base + ql.active);
     s->q.n_slots = kSlots;
     s->q.last_claim = reinterpret_cast<uint64_t*>(s->arena_base + ql.last_claim);
     s->q.closing = reinterpret_cast<uint32_t*>(s->arena_base + ql.closing);
     s->q.host_closing = s->d_flags + (size_t)kSlots * corr::kServeLine;
     s->q.host_claimed = reinterpret_cast<uint64_t*>(s->d_flags);
-    s->q.rr = reinterpret_cast<uint32_t*>(s->arena_base + ql.rr);
     s->q.idle_ticks = (uint32_t)std::max(1.0, (double)clock_khz * 1e3 * kIdleUs * 1e-6);
     s->q.max_polls = kMaxPolls;
     for (int k = kSlots - 1; k >= 0; --k) s->free_slots.push_back(k);
@@ -706,7 +716,7 @@ corr_status corr_sched_destroy(corr_sched* s) {
   // A callback may still be returning after its stream has passed it.
   while (s->callbacks.load() != 0) std::this_thread::yield();
   for (hipStream_t st : all) hipStreamDestroy(st);
-  for (hipEvent_t e : {s->ev_pub, s->ev_grid[0], s->ev_grid[1]})
+  for (hipEvent_t e : {s->ev_grid[0], s->ev_grid[1]})
     if (e) hipEventDestroy(e);
   for (hipEvent_t e : s->ev_copy_x)
     if (e) hipEventDestroy(e);

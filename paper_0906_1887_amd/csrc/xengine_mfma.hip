@@ -900,7 +900,8 @@ __device__ __forceinline__ v4i ci4_rotm(int w0, int w1) {
 // form; measured on the MI355X it runs the C3 integration ≈4 % faster (the
 // clock under load rises from ≈1.67 to ≈1.87 GHz).  A diagonal wave skips the
 // 6 strictly upper 16 x 16 blocks of its quarter.
-template <int EK, bool DIAG>
+// THROUGH: the products are only stored, through to memory (system scope).
+template <int EK, bool DIAG, bool THROUGH = false>
 __device__ __forceinline__ void mfma_tile_128_i8(const XArgs& a, int8_t* lds, int ch, int split, int I, int J) {
   constexpr int BT = 128;
   constexpr int PANEL = BT * kMKC;           // bytes per operand per stage
@@ -1164,7 +1165,10 @@ __device__ __forceinline__ void mfma_tile_128_i8(const XArgs& a, int8_t* lds, in
           // CI4 operands are 16 x the sample parts: the sums are 256 V exactly
           const int re = EK == kElemCI4 ? (vr[m][n][r] >> 8) : vr[m][n][r];
           const int im = (i == j) ? 0 : (EK == kElemCI4 ? (vi[m][n][r] >> 8) : vi[m][n][r]);
-          if (a.accumulate) {
+          if constexpr (THROUGH) {
+            __hip_atomic_store(reinterpret_cast<uint64_t*>(pp), (uint64_t)(uint32_t)re | (uint64_t)(uint32_t)im << 32,
+                               __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+          } else if (a.accumulate) {
             int2 o = *pp;
             o.x += re;
             o.y += im;
@@ -1420,6 +1424,19 @@ __global__ __launch_bounds__(256, 2) void xeng_mfma_kernel(XArgs a) {
 // the host (which then lists the job no more); the workgroup that finishes
 // the job's last item writes the job's completion word in host memory.
 //
+// A claim is one fetch-and-add on the slot's claim word.  It cannot fail, only
+// overshoot (a count past the job's items, harmless: the next job of the slot
+// sets the word anew), so the few hundred workgroups that meet on one new job
+// take its items in as many atomics.  With a compare-and-swap bounded by a
+// claim limit all but one of them failed each time: 12 jobs of 64 or 256
+// channels and 16 to 128 inputs took 940 us as a batch
+// (with one update launch for three copies a job), 700 with the add, and 460
+// once a tile's products went through to memory instead of a release fence per
+// tile (1500 at first).  A
+// workgroup whose list entry is out of date may claim an item of the slot's
+// next job: the word's generation tells, and the job record is that job's (it
+// is written before the word, and not replaced while an item is unfinished).
+//
 // A grid ends as a whole: once no workgroup has claimed an item for
 // idle_ticks of the 100 MHz wall clock, the first workgroup to notice closes
 // the grid (it raises `closing` to the grid's generation and tells the host),
@@ -1431,35 +1448,67 @@ __device__ __forceinline__ uint64_t sys_load64(const void* p) {
   return __hip_atomic_load(static_cast<const uint64_t*>(p), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
 }
 
-// Thread 0: claim one item, or return -1 when the grid has closed (or this
-// workgroup has polled max_polls times without work).
-__device__ int serve_claim(const ServeQueue& q, uint64_t* claimed) {
+// What a workgroup remembers of the list between claims.
+struct ServeView {
+  uint32_t turn;      // its place in the round robin
+  uint32_t n;         // length and version of the list when it last looked
+  uint32_t version;
+  uint64_t spent;     // places of that list whose jobs have no unclaimed item
+  bool fresh;         // this list's jobs' samples are visible (acquired since it was seen)
+};
+
+// One lane: claim one item; the slot, or -1 when the grid has closed (or this
+// workgroup has polled max_polls times without work).  *word receives the
+// claim word.  Memory takes microseconds to answer while the grid streams
+// samples, so the next entry is fetched together with the list's length, on
+// the guess that the list is the one last seen.
+__device__ int serve_claim(const ServeQueue& q, ServeView& v, uint64_t* word) {
   for (int poll = 0; poll < q.max_polls; ++poll) {
-    if (__hip_atomic_load(q.closing, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) >= q.gen) return -1;
-    const int n = __hip_atomic_load(q.active, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
-    if (n > 0 && n <= q.n_slots) {
-      const uint32_t r = __hip_atomic_fetch_add(q.rr, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      for (int a = 0; a < n; ++a) {
-        const int s = __hip_atomic_load(q.active + 1 + (int)((r + (uint32_t)a) % (uint32_t)n), __ATOMIC_RELAXED,
-                                        __HIP_MEMORY_SCOPE_SYSTEM);
-        if (s < 0 || s >= q.n_slots) continue;
-        uint64_t* cw = q.claim + (size_t)s * (kServeLine / 2);
-        const uint64_t lim = sys_load64(q.limit + (size_t)s * (kServeLine / 2));
-        uint64_t w = __hip_atomic_load(cw, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        while (w < lim) {
-          if (__hip_atomic_compare_exchange_strong(cw, &w, w + 1, __ATOMIC_RELAXED, __ATOMIC_RELAXED,
-                                                   __HIP_MEMORY_SCOPE_AGENT)) {
-            __hip_atomic_fetch_max(q.last_claim, (uint64_t)wall_clock64(), __ATOMIC_RELAXED,
-                                   __HIP_MEMORY_SCOPE_AGENT);
-            // the job's last item: tell the host, which then lists the job no more
-            if (w + 1 == lim)
-              __hip_atomic_store(q.host_claimed + (size_t)s * (kServeLine / 2) + 1, lim, __ATOMIC_RELAXED,
-                                 __HIP_MEMORY_SCOPE_SYSTEM);
-            *claimed = w;
-            return s;
-          }
-        }
+    uint32_t at = v.turn % v.n;
+    const uint32_t closing = __hip_atomic_load(q.closing, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    const uint64_t head = sys_load64(q.active);
+    uint64_t e0 = sys_load64(q.active + 1 + 2 * at), e1 = sys_load64(q.active + 2 + 2 * at);
+    if (closing >= q.gen) return -1;
+    const uint32_t n = min((uint32_t)head, (uint32_t)q.n_slots);
+    bool fetched = n == v.n;
+    if ((uint32_t)(head >> 32) != v.version || !fetched) {
+      v.version = (uint32_t)(head >> 32);
+      v.spent = 0;
+      v.fresh = false;
+      if (n > 0) v.n = n;
+    }
+    for (uint32_t a = 0; a < n; ++a, fetched = false) {
+      at = v.turn++ % n;
+      if ((v.spent >> at) & 1u) continue;
+      if (!fetched) {
+        e0 = sys_load64(q.active + 1 + 2 * at);
+        e1 = sys_load64(q.active + 2 + 2 * at);
       }
+      const uint32_t s = (uint32_t)e0;
+      if (s >= (uint32_t)q.n_slots) continue;
+      const uint64_t w = __hip_atomic_fetch_add(q.claim + (size_t)s * (kServeLine / 2), 1ull, __ATOMIC_RELAXED,
+                                                __HIP_MEMORY_SCOPE_AGENT);
+      // Claimed, unless the count is past the items of the generation's job.
+      uint32_t limit = (uint32_t)(e0 >> 32);
+      if ((uint32_t)(w >> 32) != (uint32_t)e1) {
+        const ServeJob* j = q.slots + s;
+        const uint64_t id = sys_load64(&j->flag_value);   // flag_value, gen
+        v.fresh = false;   // a job published after the list was seen
+        limit = (uint32_t)(id >> 32) == (uint32_t)(w >> 32)
+                    ? (uint32_t)__hip_atomic_load(&j->x.n_items, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM)
+                    : 0u;
+      }
+      if ((uint32_t)w >= limit) {
+        v.spent |= 1ull << at;
+        continue;
+      }
+      __hip_atomic_fetch_max(q.last_claim, (uint64_t)wall_clock64(), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      // the job's last item: tell the host, which then lists the job no more
+      if ((uint32_t)w + 1 == limit)
+        __hip_atomic_store(q.host_claimed + (size_t)s * (kServeLine / 2) + 1, w >> 32, __ATOMIC_RELAXED,
+                           __HIP_MEMORY_SCOPE_SYSTEM);
+      *word = w;
+      return (int)s;
     }
     const uint64_t last = __hip_atomic_load(q.last_claim, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     if ((uint64_t)wall_clock64() > last + q.idle_ticks) {
@@ -1486,48 +1535,105 @@ struct ServeClaim {
 __global__ __launch_bounds__(256, 2) void xeng_serve_kernel(ServeQueue q) {
   __shared__ __attribute__((aligned(1024))) int8_t lds[kMNS * 2 * 128 * kMKC];
   static_assert(sizeof(ServeClaim) <= sizeof(lds), "claim record fits in the tile buffer");
+  constexpr int kWords = sizeof(ServeJob) / 8;
+  static_assert(sizeof(ServeJob) % 8 == 0 && kWords <= 64, "one lane a word");
   ServeClaim* sc = reinterpret_cast<ServeClaim*>(lds);
   if (threadIdx.x == 0)   // a new grid counts as activity: it lingers idle_ticks before it may close
     __hip_atomic_fetch_max(q.last_claim, (uint64_t)wall_clock64(), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  ServeView view{blockIdx.x, 1, 0, 0, false};
   for (;;) {
     __syncthreads();   // the previous tile's LDS reads are done
-    if (threadIdx.x == 0) {
-      uint64_t claimed = 0;
-      const int slot = serve_claim(q, &claimed);
-      if (slot >= 0) {
-        const uint64_t* src = reinterpret_cast<const uint64_t*>(q.slots + slot);
-        uint64_t* dst = reinterpret_cast<uint64_t*>(&sc->job);
-        for (int k = 0; k < (int)(sizeof(ServeJob) / 8); ++k) dst[k] = sys_load64(src + k);
-        sc->item = (int)(claimed - sc->job.base);
+    if (threadIdx.x < 64) {
+      int slot = -1;
+      uint64_t word = 0;
+      if (threadIdx.x == 0) slot = serve_claim(q, view, &word);
+      slot = __builtin_amdgcn_readfirstlane(slot);
+      // Samples may have been written since the grid started, into memory that
+      // this CU or XCD has cached: drop what it holds, once for each list seen.
+      if (!__builtin_amdgcn_readfirstlane((int)view.fresh)) {
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "");
+        view.fresh = true;
       }
-      sc->slot = slot;
+      if (slot >= 0 && threadIdx.x < kWords)
+        reinterpret_cast<uint64_t*>(&sc->job)[threadIdx.x] =
+            sys_load64(reinterpret_cast<const uint64_t*>(q.slots + slot) + threadIdx.x);
+      if (threadIdx.x == 0) {
+        sc->item = (int)(uint32_t)word;
+        sc->slot = slot;
+      }
     }
     __syncthreads();
-    const int slot = sc->slot;
+    const int slot = __builtin_amdgcn_readfirstlane(sc->slot);
     if (slot < 0) return;
-    const XArgs a = sc->job.x;
-    const int item = sc->item;
-    uint32_t* const flag_word = sc->job.flag;
-    const uint32_t flag_value = sc->job.flag_value;
-    const uint64_t job_end = sc->job.base + (uint64_t)a.n_items;
+    // the record in scalar registers, as a kernel argument would be
+    ServeJob job;
+#pragma unroll
+    for (int k = 0; k < 2 * kWords; ++k)
+      reinterpret_cast<int*>(&job)[k] = __builtin_amdgcn_readfirstlane(reinterpret_cast<const int*>(&sc->job)[k]);
+    const XArgs& a = job.x;
+    const int item = __builtin_amdgcn_readfirstlane(sc->item);
     __syncthreads();   // everyone holds the claim before the tile reuses the buffer
     const int tile = item % a.n_tiles;
     const int ch = item / a.n_tiles;
     int I, J;
     tile_decode(tile, I, J);
-    if (I == J) mfma_tile_128_i8<kElemI8, true>(a, lds, ch, 0, I, J);
-    else mfma_tile_128_i8<kElemI8, false>(a, lds, ch, 0, I, J);
-    __threadfence();   // this thread's part of the tile is visible device-wide
+    if (I == J) mfma_tile_128_i8<kElemI8, true, true>(a, lds, ch, 0, I, J);
+    else mfma_tile_128_i8<kElemI8, false, true>(a, lds, ch, 0, I, J);
+    // The products were stored through to memory (system scope), so they are
+    // visible device-wide once each wave's stores are acknowledged; a release
+    // fence per tile would write back the whole L2 of the XCD.
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     __syncthreads();
     if (threadIdx.x == 0) {
       const uint32_t old = __hip_atomic_fetch_add(q.done + (size_t)slot * kServeLine, 1u, __ATOMIC_RELAXED,
                                                   __HIP_MEMORY_SCOPE_AGENT);
-      if ((uint64_t)old + 1 == job_end) {
+      if (old + 1 == (uint32_t)a.n_items) {
         __threadfence_system();
-        __hip_atomic_store(flag_word, flag_value, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
+        __hip_atomic_store(job.flag, job.flag_value, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
       }
     }
   }
+}
+
+// Publish a batch of admitted jobs to the queue of a running serving grid: the
+// jobs' records and done counts, then their slots' claim words (no item of a
+// job is claimed before its claim word is set, so its record is seen first),
+// then the list of active slots.  The slots' former jobs are complete.  Every
+// store goes through to memory (system scope, or an atomic) and is
+// acknowledged before the next step, so no fence has to write back an L2.  One
+// launch a batch: as three copies a job the queue updates took 8 us each on
+// the device and 25 us a job on the host.
+__global__ __launch_bounds__(256) void xeng_publish_kernel(const ServeUpdate* __restrict__ u, int n_jobs, int n_active,
+                                                           uint32_t version, ServeQueue q) {
+  constexpr int kWords = sizeof(ServeJob) / 8;
+  const uint64_t* src = reinterpret_cast<const uint64_t*>(u->job);
+  for (int k = threadIdx.x; k < n_jobs * kWords; k += 256) {
+    uint64_t* dst = reinterpret_cast<uint64_t*>(q.slots + u->slot[k / kWords]) + k % kWords;
+    __hip_atomic_store(dst, src[k], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+  }
+  const int slot = threadIdx.x < n_jobs ? u->slot[threadIdx.x] : 0;
+  const uint64_t word = threadIdx.x < n_jobs ? (uint64_t)u->job[threadIdx.x].gen << 32 : 0;
+  const uint64_t entry = threadIdx.x < 2 * n_active ? u->active[threadIdx.x] : 0;
+  if (threadIdx.x < n_jobs)
+    __hip_atomic_exchange(q.done + (size_t)slot * kServeLine, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+  __syncthreads();
+  if (threadIdx.x < n_jobs)
+    __hip_atomic_exchange(q.claim + (size_t)slot * (kServeLine / 2), word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+  __syncthreads();
+  if (threadIdx.x < 2 * n_active)
+    __hip_atomic_store(q.active + 1 + threadIdx.x, entry, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+  if (threadIdx.x == 255)
+    __hip_atomic_store(q.active, (uint64_t)version << 32 | (uint64_t)n_active, __ATOMIC_RELAXED,
+                       __HIP_MEMORY_SCOPE_SYSTEM);
+}
+
+hipError_t launch_xeng_publish(const ServeUpdate* u, int n_jobs, int n_active, uint32_t version, const ServeQueue& q,
+                               hipStream_t s) {
+  if (n_jobs > kServeSlots || n_active > kServeSlots) return hipErrorInvalidValue;
+  hipLaunchKernelGGL(xeng_publish_kernel, dim3(1), dim3(256), 0, s, u, n_jobs, n_active, version, q);
+  return hipGetLastError();
 }
 
 hipError_t launch_xeng_mfma(const XArgs& a, int elem, int bt, hipStream_t s) {
