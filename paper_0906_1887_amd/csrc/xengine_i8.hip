@@ -17,10 +17,11 @@
 // stage s + 2.
 //
 // Bound: as the aligned engine (matrix cores and the L2-to-LDS traffic).  The
-// extra register stop costs 20 % against it: 1024 inputs x 96 channels x 8001
-// samples take 2.04 ms, 8000 samples (aligned rows) 1.69 ms, and 12.5 ms when
-// the samples were loaded two bytes at a time; 231 x 524 x 2866 takes 416 us
-// (1948 before), 100 x 133 x 2001 69 us with its read-out (125 before).  Two
+// extra register stop costs 18 % against it: 1024 inputs x 96 channels x 8001
+// samples take 2.00 ms, 8000 samples (aligned rows) 1.69 ms, and 12.5 ms when
+// the samples were loaded two bytes at a time; 231 x 524 x 2866 takes 373 us
+// (1948 before; 403 with a condition around the loads of the steady loop), 100
+// x 133 x 2001 58 us with its read-out (125 before).  Two
 // stages in flight fill the registers of two waves per SIMD (254 VGPRs);
 // writing the LDS stage after the fragment reads instead of before was 1 %
 // slower.
@@ -103,14 +104,18 @@ __device__ __forceinline__ void xeng_i8u_tile(const XArgs& a, int8_t* lds, int c
   }
 
   v4i R[PF][NOP][QPW];
+  auto gload_full = [&](auto S, int st) {   // st < n_fast
+    constexpr int sl = decltype(S)::value;
+#pragma unroll
+    for (int q = 0; q < QPW; ++q)
+#pragma unroll
+      for (int o = 0; o < NOP; ++o)
+        R[sl][o][q] = load16_any<v4i>((o == 0 ? tA : tB) + (int64_t)st * kUKC + off[o][q]);
+  };
   auto gload = [&](auto S, int st) {
     constexpr int sl = decltype(S)::value;
     if (st < n_fast) {
-#pragma unroll
-      for (int q = 0; q < QPW; ++q)
-#pragma unroll
-        for (int o = 0; o < NOP; ++o)
-          R[sl][o][q] = load16_any<v4i>((o == 0 ? tA : tB) + (int64_t)st * kUKC + off[o][q]);
+      gload_full(S, st);
     } else {
 #pragma unroll
       for (int q = 0; q < QPW; ++q) {
@@ -183,28 +188,49 @@ __device__ __forceinline__ void xeng_i8u_tile(const XArgs& a, int8_t* lds, int c
   using S3 = std::integral_constant<int, PF == 4 ? 3 : 1>;
   // Stage st waits in register slot st % PF.  Iteration s moves stage s + 2 to
   // LDS, refills its slot with stage s + 2 + PF, reads the fragments of stage
-  // s + 1 and multiplies those of stage s.
-  if (0 < n_st) gload(S0{}, 0);
-  if (1 < n_st) gload(S1{}, 1);
-  if constexpr (PF == 4) {
-    if (2 < n_st) gload(S2{}, 2);
-    if (3 < n_st) gload(S3{}, 3);
+  // s + 1 and multiplies those of stage s.  FULL: all of these exist and the
+  // loaded ones lie wholly in the pass.  Without any condition around a load the
+  // compiler waits for the oldest stage only (vmcnt counts what was issued
+  // since); with one it waits for all of them.
+  // (64-row tiles gain nothing from it and would spill.)
+  const bool deep = BT == 128 && n_fast > 2 * PF + 1;
+  if (deep) {
+    gload_full(S0{}, 0);
+    gload_full(S1{}, 1);
+    if constexpr (PF == 4) {
+      gload_full(S2{}, 2);
+      gload_full(S3{}, 3);
+    }
+    lstore(S0{}, 0);
+    gload_full(S0{}, PF);
+    barrier();
+    lstore(S1{}, 1);
+    gload_full(S1{}, 1 + PF);
+  } else {
+    if (0 < n_st) gload(S0{}, 0);
+    if (1 < n_st) gload(S1{}, 1);
+    if constexpr (PF == 4) {
+      if (2 < n_st) gload(S2{}, 2);
+      if (3 < n_st) gload(S3{}, 3);
+    }
+    if (0 < n_st) lstore(S0{}, 0);
+    if (PF < n_st) gload(S0{}, PF);
+    barrier();
+    if (1 < n_st) lstore(S1{}, 1);
+    if (1 + PF < n_st) gload(S1{}, 1 + PF);
   }
-  if (0 < n_st) lstore(S0{}, 0);
-  if (PF < n_st) gload(S0{}, PF);
-  barrier();
-  if (1 < n_st) lstore(S1{}, 1);
-  if (1 + PF < n_st) gload(S1{}, 1 + PF);
   auto run = [&](auto sk, auto active) {
     constexpr bool ACT = decltype(active)::value;
     v4i af0[NB], bf0[NB], af1[NB], bf1[NB];
     if (ACT && n_st > 0) read(0, af0, bf0);
-    auto step = [&](auto U, int s) {
-      if (s + 1 < n_st) {
+    auto step = [&](auto full, auto U, int s) {
+      constexpr bool FULL = decltype(full)::value;
+      if (FULL || s + 1 < n_st) {
         barrier();
-        if (s + 2 < n_st) {
+        if (FULL || s + 2 < n_st) {
           lstore(U, s + 2);
-          if (s + 2 + PF < n_st) gload(U, s + 2 + PF);
+          if constexpr (FULL) gload_full(U, s + 2 + PF);
+          else if (s + 2 + PF < n_st) gload(U, s + 2 + PF);
         }
         if constexpr (ACT) read(s + 1, af1, bf1);
       }
@@ -217,14 +243,19 @@ __device__ __forceinline__ void xeng_i8u_tile(const XArgs& a, int8_t* lds, int c
         }
       }
     };
-    for (int s = 0; s < n_st; s += PF) {   // stage s + 2 + u waits in slot (2 + u) % PF
-      step(std::integral_constant<int, 2 % PF>{}, s);
-      if (s + 1 < n_st) step(std::integral_constant<int, 3 % PF>{}, s + 1);
+    auto steps = [&](auto full, int s) {   // stage s + 2 + u waits in slot (2 + u) % PF
+      constexpr bool FULL = decltype(full)::value;
+      step(full, std::integral_constant<int, 2 % PF>{}, s);
+      if (FULL || s + 1 < n_st) step(full, std::integral_constant<int, 3 % PF>{}, s + 1);
       if constexpr (PF == 4) {
-        if (s + 2 < n_st) step(S0{}, s + 2);
-        if (s + 3 < n_st) step(S1{}, s + 3);
+        if (FULL || s + 2 < n_st) step(full, S0{}, s + 2);
+        if (FULL || s + 3 < n_st) step(full, S1{}, s + 3);
       }
-    }
+    };
+    int s = 0;
+    if (deep)
+      for (; s + 2 * PF + 1 < n_fast; s += PF) steps(std::true_type{}, s);
+    for (; s < n_st; s += PF) steps(std::false_type{}, s);
   };
   if (DIAG && wm < wn) {
     run(std::false_type{}, std::false_type{});
