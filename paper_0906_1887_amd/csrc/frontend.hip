@@ -16,6 +16,8 @@
 // 8 lanes per FFT, a DFT16 per lane, the inner twiddles, one wave-local LDS
 // exchange, two DFT8s per lane), requantised like the real F-stage and
 // written to ring[k][input][t] for k = 0..127 in natural order (DC first).
+#include <type_traits>
+
 #include "common.h"
 #include "fft_device.h"
 #include "launch.h"
@@ -157,14 +159,14 @@ struct CArgs {
   int32_t n_ig;            // ceil(n_in / inputs per workgroup)
   float scale;
   float max_abs;
-  int32_t vec_in;          // n_in a multiple of the inputs per workgroup, volt 16-byte aligned
+  int32_t vec_in;          // n_in a multiple of the inputs per workgroup, volt aligned to half of them
   int32_t vec_out;         // t_offset, ring_stride multiples of 8, ring 16-byte aligned
   int64_t n_items;
   int64_t per_xcd;
 };
 
-// Sample (re, im) of input j (0..IN-1) from the 16 bytes a lane holds for
-// one time instant.  FMT 1: 16-bit words, 5+5 bits; FMT 2: bytes, 4+4 bits.
+// Sample (re, im) in bits `shift` .. of a word.  FMT 1: 16-bit words, 5+5 bits;
+// FMT 2: bytes, 4+4 bits.
 template <int FMT>
 __device__ __forceinline__ float2 unpack_sample(uint32_t d, int shift) {
   const uint32_t v = d >> shift;
@@ -174,18 +176,29 @@ __device__ __forceinline__ float2 unpack_sample(uint32_t d, int shift) {
     return make_float2((float)((int32_t)(v << 24) >> 28), (float)((int32_t)(v << 28) >> 28));
 }
 
-// One workgroup: 16 blocks x 8 inputs (16 bytes per time instant for 16-bit
-// words, 8 for bytes).  Slot f = tid / 8 (lanes l = tid % 8) owns block
-// f % 16 and, in round pr, input 2 pr + f / 16 (the two inputs of a round sit
-// in different waves); it loads its 16 samples x 8 inputs straight into
-// registers.  S[f] is used by the 8 lanes of slot f only, all in one wave; O
-// is the workgroup's corner turn for the round.
+// One workgroup: 16 blocks x 8 inputs.  Slot f owns block f / 2 and the half hi
+// = f % 2 of the inputs; its 8 lanes (l) load their 16 samples x 4 inputs
+// straight into registers and take one input a round.  Neighbouring lanes are
+// the two halves of one time instant, so that a pair of them reads 16 (words)
+// or 8 (bytes) consecutive bytes: every load touches as many cache lines as it
+// has lane pairs, and with a slot per wave half and all 8 inputs in each lane
+// (twice the bytes from twice the lines) the loads took as long as the
+// transforms.  S[f] is used by the 8 lanes of slot f only, all in one wave; O is
+// the workgroup's corner turn for the round, input pr of the first half beside
+// input pr of the second.
+//
+// Exchange of complex values (34 KB, three workgroups per CU) for words; of
+// real and imaginary parts in turn (17 KB, four per CU) for bytes: 3 % faster
+// there, 2 % slower for words, whose doubled input asks for L2 room.  64 inputs
+// x 10000 blocks, aggregation to dump: 305 -> 253 us (words), 156 -> 135 (bytes).
 template <int FMT>
-__global__ __launch_bounds__(256, 3) void fstage_c_kernel(CArgs a) {
+__global__ __launch_bounds__(256, FMT == 1 ? 3 : 4) void fstage_c_kernel(CArgs a) {
   constexpr int SB = (FMT == 1) ? 2 : 1;  // bytes per sample
   constexpr int IN = 8;                   // inputs per workgroup
-  constexpr int NW = 2 * SB;              // 32-bit words per time instant and lane
-  __shared__ __attribute__((aligned(16))) float2 S[kCSlots][8 * kCSRow];  // 34 KB
+  constexpr int PER = IN / 2;             // inputs per slot
+  constexpr int NW = PER * SB / 4;        // 32-bit words per time instant and lane
+  using Cell = std::conditional_t<FMT == 1, float2, float>;
+  __shared__ __attribute__((aligned(16))) Cell S[kCSlots][8 * kCSRow];     // 34 or 17 KB
   __shared__ __attribute__((aligned(16))) uint32_t O[kCN][kCORow];         // 10 KB
   __shared__ float2 tw[kCN];                                               // 1 KB
 
@@ -200,38 +213,37 @@ __global__ __launch_bounds__(256, 3) void fstage_c_kernel(CArgs a) {
   const int64_t b0 = ((rest / a.n_ig) * 4 + (item & 3)) * kCBlk;
   if (b0 >= a.n_blocks) return;
   const int i0 = ig * IN;
-  const int f = tid >> 3;
-  const int l = tid & 7;
-  const int blk = f & (kCBlk - 1);
-  const int hi = f >> 4;  // which input of the round's pair (uniform per wave)
+  const int hi = tid & 1;        // which half of the inputs
+  const int l = (tid >> 1) & 7;
+  const int blk = tid >> 4;
+  const int f = 2 * blk + hi;
   const int64_t nb = min((int64_t)kCBlk, a.n_blocks - b0);
 
-  // Samples t = l + 8 n2 of block b0 + blk, inputs i0..i0+IN-1 (zero outside).
+  // Samples t = l + 8 n2 of block b0 + blk, inputs i0 + hi PER .. (zero outside).
   uint32_t w[16][NW];
   if (a.vec_in && nb == kCBlk) {
-    const uint8_t* p = a.volt + (((b0 + blk) * kCN + l) * a.n_in + i0) * SB;
+    const uint8_t* p = a.volt + (((b0 + blk) * kCN + l) * a.n_in + i0 + hi * PER) * SB;
 #pragma unroll
     for (int n2 = 0; n2 < 16; ++n2) {
       const uint8_t* q = p + (int64_t)n2 * 8 * a.n_in * SB;
-      if constexpr (NW == 4) {
-        const uint4 v = *reinterpret_cast<const uint4*>(q);
-        w[n2][0] = v.x; w[n2][1] = v.y; w[n2][2] = v.z; w[n2][3] = v.w;
-      } else {
+      if constexpr (NW == 2) {
         const uint2 v = *reinterpret_cast<const uint2*>(q);
         w[n2][0] = v.x; w[n2][1] = v.y;
+      } else {
+        w[n2][0] = *reinterpret_cast<const uint32_t*>(q);
       }
     }
   } else {
 #pragma unroll
     for (int n2 = 0; n2 < 16; ++n2) {
       const int64_t t = (b0 + blk) * kCN + l + 8 * n2;
-      const uint8_t* p = a.volt + (t * a.n_in + i0) * SB;
+      const uint8_t* p = a.volt + (t * a.n_in + i0 + hi * PER) * SB;
 #pragma unroll
       for (int j = 0; j < NW; ++j) {
         uint32_t v = 0;
         for (int q = 0; q < 4; ++q) {
           const int byte = 4 * j + q;
-          if (blk < nb && i0 + byte / SB < a.n_in) v |= (uint32_t)p[byte] << (8 * q);
+          if (blk < nb && i0 + hi * PER + byte / SB < a.n_in) v |= (uint32_t)p[byte] << (8 * q);
         }
         w[n2][j] = v;
       }
@@ -242,83 +254,88 @@ __global__ __launch_bounds__(256, 3) void fstage_c_kernel(CArgs a) {
   const float h = a.scale;
   const float lo = kRqMagic - a.max_abs, hi_b = kRqMagic + a.max_abs;
 
-  // One round per input pair.  This slot's sample of round pr sits in word 0
-  // at bit 16 hi (16-bit words) or 8 hi (bytes); after a round the next pair
-  // is brought there (words move down; for bytes, every other round shifts
-  // word 0 down by 16 bits instead).  Fully unrolled, those moves become
-  // register renames.
-  const int shift = (FMT == 1) ? 16 * hi : 8 * hi;
+  // One round per input of a slot.
 #pragma unroll
-  for (int pr = 0; pr < IN / 2; ++pr) {
-    {
-      float2 x[16], X[16];
+  for (int pr = 0; pr < PER; ++pr) {
+    float2 x[16], X[16];
 #pragma unroll
-      for (int n2 = 0; n2 < 16; ++n2) x[n2] = unpack_sample<FMT>(w[n2][0], shift);
-      // Pass 1: lane n1 = l transforms x[n1 + 8 n2] over n2; inner twiddle W_128^(n1 k2).
-      dft16(x, X);
-      if (pr == 0) __syncthreads();  // tw is complete
+    for (int n2 = 0; n2 < 16; ++n2) x[n2] = unpack_sample<FMT>(w[n2][pr * SB / 4], 8 * (pr * SB % 4));
+    // Pass 1: lane n1 = l transforms x[n1 + 8 n2] over n2; inner twiddle W_128^(n1 k2).
+    dft16(x, X);
+    if (pr == 0) __syncthreads();  // tw is complete
+    // The exchange: lane l takes n1 = 0..7 for k2 = l and for k2 = l + 8.
+    if constexpr (FMT == 1) {
       S[f][l * kCSRow] = X[0];
 #pragma unroll
       for (int k2 = 1; k2 < 16; ++k2) S[f][l * kCSRow + k2] = cmul(X[k2], tw[(l * k2) & (kCN - 1)]);
       wave_sync();
-      // Pass 2: DFT8 over n1 for k2 = l and then k2 = l + 8; output
-      // k = k2 + 16 k1, requantised into O (the 16-bit half of this slot's
-      // input).
-      const int i = i0 + 2 * pr + hi;
-      const int64_t blk_g = b0 + blk;
-#pragma unroll
-      for (int h2 = 0; h2 < 2; ++h2) {
-        float2 y[8], z[8];
-#pragma unroll
-        for (int n1 = 0; n1 < 8; ++n1) y[n1] = S[f][n1 * kCSRow + l + 8 * h2];
-        dft8(y, z);
-#pragma unroll
-        for (int k1 = 0; k1 < 8; ++k1) {
-          const int k = l + 8 * h2 + 16 * k1;
-          const uint32_t code = __builtin_amdgcn_perm(requant_bits(z[k1].y, h, lo, hi_b),
-                                                      requant_bits(z[k1].x, h, lo, hi_b), 0x0c0c0400u);
-          reinterpret_cast<uint16_t*>(&O[k][blk])[hi] = (uint16_t)code;
-          if (a.dbg != nullptr && blk_g < a.n_blocks && i < a.n_in)
-            reinterpret_cast<float2*>(a.dbg)[((int64_t)k * a.n_in + i) * a.n_blocks + blk_g] = z[k1];
-        }
-      }
-      __syncthreads();
-      // Write the pair's rows ring[k][input][t_offset + b0 ..] (32 bytes
-      // each) as 16-byte pieces, two neighbouring lanes per row; a piece
-      // holds the il-th 16-bit half of O[k][8 half .. 8 half + 7].
-#pragma unroll
-      for (int j = 0; j < 2; ++j) {
-        const int pc = tid + 256 * j;
-        const int hf = pc & 1, row = pc >> 1;
-        const int k = row >> 1, il = row & 1;
-        const int io = i0 + 2 * pr + il;
-        if (io < a.n_in) {
-          uint16_t* dst = reinterpret_cast<uint16_t*>(a.ring) + ((int64_t)k * a.n_in + io) * a.ring_stride +
-                          a.t_offset + b0 + 8 * hf;
-          const uint4* src = reinterpret_cast<const uint4*>(&O[k][8 * hf]);
-          const uint4 q0 = src[0], q1 = src[1];
-          const uint32_t sel = il ? 0x07060302u : 0x05040100u;
-          const uint4 o = make_uint4(__builtin_amdgcn_perm(q0.y, q0.x, sel), __builtin_amdgcn_perm(q0.w, q0.z, sel),
-                                     __builtin_amdgcn_perm(q1.y, q1.x, sel), __builtin_amdgcn_perm(q1.w, q1.z, sel));
-          if (a.vec_out && nb == kCBlk) {
-            *reinterpret_cast<uint4*>(dst) = o;
-          } else {
-            const uint32_t v[4] = {o.x, o.y, o.z, o.w};
-            for (int q = 0; q < 8 && 8 * hf + q < nb; ++q) dst[q] = (uint16_t)(v[q >> 1] >> (16 * (q & 1)));
-          }
-        }
-      }
-      __syncthreads();
-    }
-    if (FMT == 2 && (pr & 1) == 0) {
-#pragma unroll
-      for (int n2 = 0; n2 < 16; ++n2) w[n2][0] >>= 16;
     } else {
 #pragma unroll
-      for (int n2 = 0; n2 < 16; ++n2)
+      for (int k2 = 1; k2 < 16; ++k2) X[k2] = cmul(X[k2], tw[(l * k2) & (kCN - 1)]);
 #pragma unroll
-        for (int j = 0; j + 1 < NW; ++j) w[n2][j] = w[n2][j + 1];
+      for (int k2 = 0; k2 < 16; ++k2) S[f][l * kCSRow + k2] = X[k2].x;
+      wave_sync();
+#pragma unroll
+      for (int n = 0; n < 16; ++n) x[n].x = S[f][(n & 7) * kCSRow + l + (n & 8)];
+      wave_sync();
+#pragma unroll
+      for (int k2 = 0; k2 < 16; ++k2) S[f][l * kCSRow + k2] = X[k2].y;
+      wave_sync();
+#pragma unroll
+      for (int n = 0; n < 16; ++n) x[n].y = S[f][(n & 7) * kCSRow + l + (n & 8)];
+      wave_sync();
     }
+    // Pass 2: DFT8 over n1 for k2 = l and then k2 = l + 8; output
+    // k = k2 + 16 k1, requantised into O (the 16-bit half of this slot's
+    // input).
+    const int i = i0 + hi * PER + pr;
+    const int64_t blk_g = b0 + blk;
+#pragma unroll
+    for (int h2 = 0; h2 < 2; ++h2) {
+      float2 y[8], z[8];
+#pragma unroll
+      for (int n1 = 0; n1 < 8; ++n1) {
+        if constexpr (FMT == 1) y[n1] = S[f][n1 * kCSRow + l + 8 * h2];
+        else y[n1] = x[n1 + 8 * h2];
+      }
+      dft8(y, z);
+#pragma unroll
+      for (int k1 = 0; k1 < 8; ++k1) {
+        const int k = l + 8 * h2 + 16 * k1;
+        const uint32_t code = __builtin_amdgcn_perm(requant_bits(z[k1].y, h, lo, hi_b),
+                                                    requant_bits(z[k1].x, h, lo, hi_b), 0x0c0c0400u);
+        reinterpret_cast<uint16_t*>(&O[k][blk])[hi] = (uint16_t)code;
+        if (a.dbg != nullptr && blk_g < a.n_blocks && i < a.n_in)
+          reinterpret_cast<float2*>(a.dbg)[((int64_t)k * a.n_in + i) * a.n_blocks + blk_g] = z[k1];
+      }
+    }
+    __syncthreads();
+    // Write the round's rows ring[k][input][t_offset + b0 ..] (32 bytes
+    // each) as 16-byte pieces, two neighbouring lanes per row; a piece
+    // holds the il-th 16-bit half of O[k][8 half .. 8 half + 7].
+#pragma unroll
+    for (int j = 0; j < 2; ++j) {
+      const int pc = tid + 256 * j;
+      const int hf = pc & 1, row = pc >> 1;
+      const int k = row >> 1, il = row & 1;
+      const int io = i0 + il * PER + pr;
+      if (io < a.n_in) {
+        uint16_t* dst = reinterpret_cast<uint16_t*>(a.ring) + ((int64_t)k * a.n_in + io) * a.ring_stride +
+                        a.t_offset + b0 + 8 * hf;
+        const uint4* src = reinterpret_cast<const uint4*>(&O[k][8 * hf]);
+        const uint4 q0 = src[0], q1 = src[1];
+        const uint32_t sel = il ? 0x07060302u : 0x05040100u;
+        const uint4 o = make_uint4(__builtin_amdgcn_perm(q0.y, q0.x, sel), __builtin_amdgcn_perm(q0.w, q0.z, sel),
+                                   __builtin_amdgcn_perm(q1.y, q1.x, sel), __builtin_amdgcn_perm(q1.w, q1.z, sel));
+        if (a.vec_out && nb == kCBlk) {
+          *reinterpret_cast<uint4*>(dst) = o;
+        } else {
+          const uint32_t v[4] = {o.x, o.y, o.z, o.w};
+          for (int q = 0; q < 8 && 8 * hf + q < nb; ++q) dst[q] = (uint16_t)(v[q >> 1] >> (16 * (q & 1)));
+        }
+      }
+    }
+    __syncthreads();
   }
 }
 
@@ -338,7 +355,7 @@ hipError_t launch_fstage_complex(const FStageCall& c, hipStream_t s) {
   a.n_ig = (c.n_in + in - 1) / in;
   a.scale = c.scale;
   a.max_abs = c.max_abs;
-  a.vec_in = (c.n_in % in == 0) && ((reinterpret_cast<uintptr_t>(c.volt) & (in * sb - 1)) == 0);
+  a.vec_in = (c.n_in % in == 0) && ((reinterpret_cast<uintptr_t>(c.volt) & (in / 2 * sb - 1)) == 0);
   a.vec_out = (c.t_offset % 8 == 0) && (c.ring_stride % 8 == 0) && ((reinterpret_cast<uintptr_t>(c.ring) & 15) == 0);
   const int64_t n_bg = (c.n_blocks + kCBlk - 1) / kCBlk;
   a.n_items = (n_bg + 3) / 4 * 4 * a.n_ig;   // block groups padded to whole lines
