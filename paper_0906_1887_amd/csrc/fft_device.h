@@ -8,6 +8,12 @@
 
 namespace corr {
 
+// 8 inputs per workgroup of an F-stage over n_bg groups of 16 blocks, or 4 where
+// 8 make fewer than `full` workgroups (see the launchers).
+inline int fstage_inputs(int64_t n_bg, int n_in, int64_t full) {
+  return n_bg * ((n_in + 7) / 8) >= full ? 8 : 4;
+}
+
 __device__ __forceinline__ float2 cadd(float2 a, float2 b) { return make_float2(a.x + b.x, a.y + b.y); }
 __device__ __forceinline__ float2 csub(float2 a, float2 b) { return make_float2(a.x - b.x, a.y - b.y); }
 __device__ __forceinline__ float2 cmul(float2 a, float2 w) {

@@ -159,7 +159,7 @@ struct CArgs {
   int32_t n_ig;            // ceil(n_in / inputs per workgroup)
   float scale;
   float max_abs;
-  int32_t vec_in;          // n_in a multiple of the inputs per workgroup, volt aligned to half of them
+  int32_t vec_in;          // n_in a multiple of the inputs per workgroup, volt aligned to half their bytes
   int32_t vec_out;         // t_offset, ring_stride multiples of 8, ring 16-byte aligned
   int64_t n_items;
   int64_t per_xcd;
@@ -176,8 +176,8 @@ __device__ __forceinline__ float2 unpack_sample(uint32_t d, int shift) {
     return make_float2((float)((int32_t)(v << 24) >> 28), (float)((int32_t)(v << 28) >> 28));
 }
 
-// One workgroup: 16 blocks x 8 inputs.  Slot f owns block f / 2 and the half hi
-// = f % 2 of the inputs; its 8 lanes (l) load their 16 samples x 4 inputs
+// One workgroup: 16 blocks x IN inputs (8, or 4).  Slot f owns block f / 2 and the half hi
+// = f % 2 of the inputs; its 8 lanes (l) load their 16 samples x IN / 2 inputs
 // straight into registers and take one input a round.  Neighbouring lanes are
 // the two halves of one time instant, so that a pair of them reads 16 (words)
 // or 8 (bytes) consecutive bytes: every load touches as many cache lines as it
@@ -191,12 +191,13 @@ __device__ __forceinline__ float2 unpack_sample(uint32_t d, int shift) {
 // real and imaginary parts in turn (17 KB, four per CU) for bytes: 3 % faster
 // there, 2 % slower for words, whose doubled input asks for L2 room.  64 inputs
 // x 10000 blocks, aggregation to dump: 305 -> 253 us (words), 156 -> 135 (bytes).
-template <int FMT>
+template <int FMT, int IN>
 __global__ __launch_bounds__(256, FMT == 1 ? 3 : 4) void fstage_c_kernel(CArgs a) {
+  static_assert(IN == 4 || IN == 8, "inputs per workgroup");
   constexpr int SB = (FMT == 1) ? 2 : 1;  // bytes per sample
-  constexpr int IN = 8;                   // inputs per workgroup
   constexpr int PER = IN / 2;             // inputs per slot
-  constexpr int NW = PER * SB / 4;        // 32-bit words per time instant and lane
+  constexpr int NB = PER * SB;            // bytes per time instant and lane (2, 4 or 8)
+  constexpr int NW = (NB + 3) / 4;        // 32-bit words that hold them
   using Cell = std::conditional_t<FMT == 1, float2, float>;
   __shared__ __attribute__((aligned(16))) Cell S[kCSlots][8 * kCSRow];     // 34 or 17 KB
   __shared__ __attribute__((aligned(16))) uint32_t O[kCN][kCORow];         // 10 KB
@@ -229,8 +230,10 @@ __global__ __launch_bounds__(256, FMT == 1 ? 3 : 4) void fstage_c_kernel(CArgs a
       if constexpr (NW == 2) {
         const uint2 v = *reinterpret_cast<const uint2*>(q);
         w[n2][0] = v.x; w[n2][1] = v.y;
-      } else {
+      } else if constexpr (NB == 4) {
         w[n2][0] = *reinterpret_cast<const uint32_t*>(q);
+      } else {
+        w[n2][0] = *reinterpret_cast<const uint16_t*>(q);
       }
     }
   } else {
@@ -243,7 +246,7 @@ __global__ __launch_bounds__(256, FMT == 1 ? 3 : 4) void fstage_c_kernel(CArgs a
         uint32_t v = 0;
         for (int q = 0; q < 4; ++q) {
           const int byte = 4 * j + q;
-          if (blk < nb && i0 + hi * PER + byte / SB < a.n_in) v |= (uint32_t)p[byte] << (8 * q);
+          if (byte < NB && blk < nb && i0 + hi * PER + byte / SB < a.n_in) v |= (uint32_t)p[byte] << (8 * q);
         }
         w[n2][j] = v;
       }
@@ -342,7 +345,10 @@ __global__ __launch_bounds__(256, FMT == 1 ? 3 : 4) void fstage_c_kernel(CArgs a
 hipError_t launch_fstage_complex(const FStageCall& c, hipStream_t s) {
   if (c.format != 1 && c.format != 2) return hipErrorInvalidValue;
   const int sb = (c.format == 1) ? 2 : 1;
-  const int in = 8;
+  const int64_t n_bg = (c.n_blocks + kCBlk - 1) / kCBlk;
+  // words, F-stage to dump, 8 and 4 inputs per workgroup: 32 inputs x 127 blocks
+  // 59 and 46 us, 64 x 1000 71 and 66, 64 x 1900 88 and 90 (bytes 63 and 66)
+  const int in = fstage_inputs(n_bg, c.n_in, 768);
   CArgs a;
   a.volt = reinterpret_cast<const uint8_t*>(c.volt);
   a.twiddle = c.twiddle;
@@ -357,16 +363,18 @@ hipError_t launch_fstage_complex(const FStageCall& c, hipStream_t s) {
   a.max_abs = c.max_abs;
   a.vec_in = (c.n_in % in == 0) && ((reinterpret_cast<uintptr_t>(c.volt) & (in / 2 * sb - 1)) == 0);
   a.vec_out = (c.t_offset % 8 == 0) && (c.ring_stride % 8 == 0) && ((reinterpret_cast<uintptr_t>(c.ring) & 15) == 0);
-  const int64_t n_bg = (c.n_blocks + kCBlk - 1) / kCBlk;
   a.n_items = (n_bg + 3) / 4 * 4 * a.n_ig;   // block groups padded to whole lines
   if (a.n_items <= 0) return hipSuccess;
   a.per_xcd = (a.n_items + kNumXcd - 1) / kNumXcd;
   const int64_t grid = a.per_xcd * kNumXcd;
   if (grid > 0x7FFFFFFF) return hipErrorInvalidValue;
-  if (c.format == 1)
-    hipLaunchKernelGGL(fstage_c_kernel<1>, dim3((unsigned)grid), dim3(256), 0, s, a);
-  else
-    hipLaunchKernelGGL(fstage_c_kernel<2>, dim3((unsigned)grid), dim3(256), 0, s, a);
+#define CORR_FSTAGE_C(F, N) hipLaunchKernelGGL((fstage_c_kernel<F, N>), dim3((unsigned)grid), dim3(256), 0, s, a)
+  if (c.format == 1) {
+    if (in == 8) CORR_FSTAGE_C(1, 8); else CORR_FSTAGE_C(1, 4);
+  } else {
+    if (in == 8) CORR_FSTAGE_C(2, 8); else CORR_FSTAGE_C(2, 4);
+  }
+#undef CORR_FSTAGE_C
   return hipGetLastError();
 }
 

@@ -57,7 +57,7 @@ __device__ __forceinline__ float sbyte(uint32_t w) {
   return (float)((int32_t)(w << (24 - 8 * J)) >> 24);
 }
 
-// One workgroup: 16 consecutive blocks x IN inputs (IN = 8 or 16, IN / 2
+// One workgroup: 16 consecutive blocks x IN inputs (IN = 4, 8 or 16, IN / 2
 // pairs).  FFT slot f = tid / 16 (lanes l = tid % 16) owns block f: it loads
 // its 16 samples x IN inputs straight into registers (IN bytes of each
 // n_in-byte time row; more inputs per workgroup means fewer, fuller cache
@@ -89,10 +89,10 @@ __device__ __forceinline__ uint32_t pair_f16(uint32_t v) {
 // (binary16 operand, FP32 product and sum) per tap and sample.
 template <int IN, int TAPS>
 __global__ __launch_bounds__(256, 3) void fstage_kernel(FArgs a) {
-  static_assert(IN == 8 || IN == 16, "inputs per workgroup");
+  static_assert(IN == 4 || IN == 8 || IN == 16, "inputs per workgroup");
   // (16 inputs with the filterbank need more than the 256 registers of two
   // workgroups per CU: measured spills)
-  static_assert(TAPS == 1 || IN == 8, "the filterbank path takes 8 inputs per workgroup");
+  static_assert(TAPS == 1 || IN <= 8, "the filterbank path takes at most 8 inputs per workgroup");
   constexpr int kW = IN / 4;  // words per sample and lane
   __shared__ __attribute__((aligned(16))) float2 S[kFFtPerRound][kFSRow * 16];  // 34 KB
   __shared__ __attribute__((aligned(16))) uint32_t O[kFCh][kORow];              // 10 KB
@@ -143,9 +143,11 @@ __global__ __launch_bounds__(256, 3) void fstage_kernel(FArgs a) {
         if constexpr (IN == 16) {
           const uint4 u = *reinterpret_cast<const uint4*>(q);
           v[n2][0] = u.x; v[n2][1] = u.y; v[n2][2] = u.z; v[n2][3] = u.w;
-        } else {
+        } else if constexpr (IN == 8) {
           const uint2 u = *reinterpret_cast<const uint2*>(q);
           v[n2][0] = u.x; v[n2][1] = u.y;
+        } else {
+          v[n2][0] = *reinterpret_cast<const uint32_t*>(q);
         }
       }
     } else {
@@ -195,9 +197,9 @@ __global__ __launch_bounds__(256, 3) void fstage_kernel(FArgs a) {
   // Groups of 4 pairs (8 inputs, two words per sample); after a group the
   // next two words move down so that every round reads w[.][0..1].
 #pragma unroll 1
-  for (int g = 0; g < IN / 8; ++g) {
+  for (int g = 0; g < (IN + 7) / 8; ++g) {
 #pragma unroll
-    for (int r = 0; r < 4; ++r) {
+    for (int r = 0; r < (IN < 8 ? IN / 2 : 4); ++r) {
       const int pr = 4 * g + r;
       // Pass 1: lane n1 = l transforms z[n1 + 16 n2] over n2, z = a + i b.
       float2 x[16], X[16];
@@ -321,12 +323,18 @@ __global__ __launch_bounds__(256, 3) void fstage_kernel(FArgs a) {
   }
 }
 
-// 16 inputs per workgroup when n_in is a multiple of 16 (plain transform),
-// else 8; the filterbank path (taps > 1, this build: 4) takes 8.
+// Inputs per workgroup.  A workgroup's time goes with its inputs and the GPU
+// holds 768 at once (512 of 16 inputs), so a call that leaves CUs idle takes
+// fewer inputs per workgroup; a large one takes 16, whose requests fill twice
+// the part of a line.  64 inputs, F-stage to dump, with 16 / 8 / 4 inputs:
+// 100 blocks 62 / 44 / 34 us, 1000 blocks 78 / 61 / 57, 1900 blocks 81 with 8
+// and 75 with 4, 4000 blocks 86 / 84 and from there 16 is level or better.  The
+// filterbank path takes at most 8: 100 blocks 50 us with 8 and 37 with 4, 1900
+// blocks 91 and 84.
 hipError_t launch_fstage(const FArgs& a, int taps, hipStream_t s) {
   if (taps != 1 && taps != 4) return hipErrorInvalidValue;
-  const int in = (taps == 1 && a.n_in % 16 == 0) ? 16 : 8;
   const int64_t n_bg = (a.n_blocks + kFBlk - 1) / kFBlk;
+  const int in = (taps == 1 && a.n_in % 16 == 0 && n_bg * (a.n_in / 16) >= 1024) ? 16 : fstage_inputs(n_bg, a.n_in, 1024);
   FArgs b = a;
   b.n_ig = (a.n_in + in - 1) / in;
   b.vec_in = (a.n_in % in == 0) && ((reinterpret_cast<uintptr_t>(a.volt) & (in - 1)) == 0);
@@ -335,12 +343,15 @@ hipError_t launch_fstage(const FArgs& a, int taps, hipStream_t s) {
   b.per_xcd = (b.n_items + kNumXcd - 1) / kNumXcd;
   const int64_t grid = b.per_xcd * kNumXcd;
   if (grid > 0x7FFFFFFF) return hipErrorInvalidValue;
-  if (taps == 4)
-    hipLaunchKernelGGL((fstage_kernel<8, 4>), dim3((unsigned)grid), dim3(256), 0, s, b);
-  else if (in == 16)
-    hipLaunchKernelGGL((fstage_kernel<16, 1>), dim3((unsigned)grid), dim3(256), 0, s, b);
-  else
-    hipLaunchKernelGGL((fstage_kernel<8, 1>), dim3((unsigned)grid), dim3(256), 0, s, b);
+#define CORR_FSTAGE(N, T) hipLaunchKernelGGL((fstage_kernel<N, T>), dim3((unsigned)grid), dim3(256), 0, s, b)
+  if (taps == 4) {
+    if (in == 8) CORR_FSTAGE(8, 4); else CORR_FSTAGE(4, 4);
+  } else if (in == 16) {
+    CORR_FSTAGE(16, 1);
+  } else {
+    if (in == 8) CORR_FSTAGE(8, 1); else CORR_FSTAGE(4, 1);
+  }
+#undef CORR_FSTAGE
   return hipGetLastError();
 }
 
