@@ -37,14 +37,18 @@ __device__ __forceinline__ void tile_decode(int t, int& I, int& J) {
   J = t - i * (i + 1) / 2;
 }
 
-// 16 bytes from an address of any alignment, as one load (global memory takes
-// unaligned 16-byte loads on gfx950 under this ABI).
+// sizeof(V) bytes from an address of any alignment, as one load (global memory
+// takes unaligned loads on gfx950 under this ABI).
+template <typename V>
+__device__ __forceinline__ V load_any(const void* p) {
+  V v;
+  __builtin_memcpy(&v, p, sizeof(V));
+  return v;
+}
 template <typename V>
 __device__ __forceinline__ V load16_any(const void* p) {
   static_assert(sizeof(V) == 16, "16 bytes");
-  V v;
-  __builtin_memcpy(&v, p, 16);
-  return v;
+  return load_any<V>(p);
 }
 
 __device__ __forceinline__ int64_t tri_index(int64_t i, int64_t j) { return i * (i + 1) / 2 + j; }

@@ -9,9 +9,21 @@
 namespace corr {
 
 // 8 inputs per workgroup of an F-stage over n_bg groups of 16 blocks, or 4 where
-// 8 make fewer than `full` workgroups (see the launchers).
+// 8 make fewer than `full` workgroups (see the launchers) or would not divide
+// n_in: 20 real inputs x 10000 blocks 83 us with 8 and 78 with 4, filterbank 101
+// and 91, 60 byte inputs x 5000 blocks 90 and 84; 62 real inputs 96 and 102.
 inline int fstage_inputs(int64_t n_bg, int n_in, int64_t full) {
-  return n_bg * ((n_in + 7) / 8) >= full ? 8 : 4;
+  return n_in % 8 == 0 && n_bg * (n_in / 8) >= full ? 8 : 4;
+}
+
+// How an F-stage reads groups of `in` inputs of a row of n_in, `lane` of them a load.
+enum class FGroups : int32_t {
+  kFull,   // every group is full
+  kShift,  // a load that would leave the row takes the row's last inputs and shifts them down
+  kFew,    // fewer inputs than a load takes
+};
+inline FGroups fstage_groups(int n_in, int in, int lane) {
+  return n_in % in == 0 ? FGroups::kFull : n_in >= lane ? FGroups::kShift : FGroups::kFew;
 }
 
 __device__ __forceinline__ float2 cadd(float2 a, float2 b) { return make_float2(a.x + b.x, a.y + b.y); }

@@ -159,7 +159,7 @@ struct CArgs {
   int32_t n_ig;            // ceil(n_in / inputs per workgroup)
   float scale;
   float max_abs;
-  int32_t vec_in;          // n_in a multiple of the inputs per workgroup, volt aligned to half their bytes
+  FGroups groups;          // how the input groups lie in a row
   int32_t vec_out;         // t_offset, ring_stride multiples of 8, ring 16-byte aligned
   int64_t n_items;
   int64_t per_xcd;
@@ -218,38 +218,43 @@ __global__ __launch_bounds__(256, FMT == 1 ? 3 : 4) void fstage_c_kernel(CArgs a
   const int l = (tid >> 1) & 7;
   const int blk = tid >> 4;
   const int f = 2 * blk + hi;
-  const int64_t nb = min((int64_t)kCBlk, a.n_blocks - b0);
+  const int nb = (int)min((int64_t)kCBlk, a.n_blocks - b0);
 
-  // Samples t = l + 8 n2 of block b0 + blk, inputs i0 + hi PER .. (zero outside).
+  // Samples t = l + 8 n2 of block b0 + blk, inputs i0 + hi PER .., at any
+  // alignment; what is there past n_in is not written.
+  // A block past the end is the last one again, whose codes are not written.
+  const int64_t row0 = (b0 + min(blk, nb - 1)) * kCN + l;
   uint32_t w[16][NW];
-  if (a.vec_in && nb == kCBlk) {
-    const uint8_t* p = a.volt + (((b0 + blk) * kCN + l) * a.n_in + i0 + hi * PER) * SB;
+  if (IN != 4 || a.groups == FGroups::kFull) {
+    const uint8_t* p = a.volt + (row0 * a.n_in + i0 + hi * PER) * SB;
 #pragma unroll
     for (int n2 = 0; n2 < 16; ++n2) {
       const uint8_t* q = p + (int64_t)n2 * 8 * a.n_in * SB;
       if constexpr (NW == 2) {
-        const uint2 v = *reinterpret_cast<const uint2*>(q);
+        const uint2 v = load_any<uint2>(q);
         w[n2][0] = v.x; w[n2][1] = v.y;
       } else if constexpr (NB == 4) {
-        w[n2][0] = *reinterpret_cast<const uint32_t*>(q);
+        w[n2][0] = load_any<uint32_t>(q);
       } else {
-        w[n2][0] = *reinterpret_cast<const uint16_t*>(q);
+        w[n2][0] = load_any<uint16_t>(q);
       }
     }
-  } else {
+  } else if (a.groups == FGroups::kShift) {
+    // A slot whose inputs are not all there reads the row's last PER inputs and
+    // shifts them down, so that every load stays in its row.
+    const int ih = i0 + hi * PER, at = min(ih, a.n_in - PER);
+    const int sh = 8 * SB * min(PER, ih - at);  // bits; everything where the slot has no input
+    const uint8_t* p = a.volt + (row0 * a.n_in + at) * SB;
 #pragma unroll
     for (int n2 = 0; n2 < 16; ++n2) {
-      const int64_t t = (b0 + blk) * kCN + l + 8 * n2;
-      const uint8_t* p = a.volt + (t * a.n_in + i0 + hi * PER) * SB;
-#pragma unroll
-      for (int j = 0; j < NW; ++j) {
-        uint32_t v = 0;
-        for (int q = 0; q < 4; ++q) {
-          const int byte = 4 * j + q;
-          if (byte < NB && blk < nb && i0 + hi * PER + byte / SB < a.n_in) v |= (uint32_t)p[byte] << (8 * q);
-        }
-        w[n2][j] = v;
-      }
+      const uint8_t* q = p + (int64_t)n2 * 8 * a.n_in * SB;
+      if constexpr (NB == 2) w[n2][0] = (uint32_t)load_any<uint16_t>(q) >> sh;
+      else w[n2][0] = (uint32_t)((uint64_t)load_any<uint32_t>(q) >> sh);
+    }
+  } else {  // one input in all (hi 1 computes on it too, and writes nothing)
+    for (int n2 = 0; n2 < 16; ++n2) {
+      const uint8_t* p = a.volt + (row0 + 8 * n2) * SB;
+      w[n2][0] = SB == 2 ? load_any<uint16_t>(p) : *p;
     }
   }
   if (tid < kCN) tw[tid] = a.twiddle[tid];
@@ -361,7 +366,7 @@ hipError_t launch_fstage_complex(const FStageCall& c, hipStream_t s) {
   a.n_ig = (c.n_in + in - 1) / in;
   a.scale = c.scale;
   a.max_abs = c.max_abs;
-  a.vec_in = (c.n_in % in == 0) && ((reinterpret_cast<uintptr_t>(c.volt) & (in / 2 * sb - 1)) == 0);
+  a.groups = fstage_groups(c.n_in, in, in / 2);
   a.vec_out = (c.t_offset % 8 == 0) && (c.ring_stride % 8 == 0) && ((reinterpret_cast<uintptr_t>(c.ring) & 15) == 0);
   a.n_items = (n_bg + 3) / 4 * 4 * a.n_ig;   // block groups padded to whole lines
   if (a.n_items <= 0) return hipSuccess;

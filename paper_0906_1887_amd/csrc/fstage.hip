@@ -37,7 +37,7 @@ struct FArgs {
   int32_t n_ig;            // input groups = ceil(n_in / inputs per workgroup)
   float scale;             // requantisation scale s
   float max_abs;
-  int32_t vec_in;          // 1: n_in a multiple of, and volt aligned to, the inputs per workgroup
+  FGroups groups;          // how the input groups lie in a row
   int32_t vec_out;         // 1: t_offset % 8 == 0 and ring_stride % 8 == 0
   int64_t n_items;         // block groups (padded to a multiple of 4) x input groups
   int64_t per_xcd;         // ceil(n_items / 8)
@@ -61,7 +61,10 @@ __device__ __forceinline__ float sbyte(uint32_t w) {
 // pairs).  FFT slot f = tid / 16 (lanes l = tid % 16) owns block f: it loads
 // its 16 samples x IN inputs straight into registers (IN bytes of each
 // n_in-byte time row; more inputs per workgroup means fewer, fuller cache
-// line requests) and runs one 256-point FFT per pair.  The exchange buffer
+// line requests; rows of any length and alignment: with a byte at a time for
+// n_in not a multiple of IN or a ragged last block group, 60 inputs x 5000
+// blocks took 177 us instead of 95, 128 x 3500 191 instead of 167) and runs one
+// 256-point FFT per pair.  The exchange buffer
 // S[f] is used by the 16 lanes of slot f only, all in one wave; O is the
 // workgroup's corner turn for the current pair.
 constexpr int kORow = 20;  // words per channel row of O (16 blocks + pad, 16-byte aligned rows)
@@ -121,49 +124,51 @@ __global__ __launch_bounds__(256, 3) void fstage_kernel(FArgs a) {
   const int i0 = ig * IN;
   const int f = tid >> 4;  // block of this FFT slot
   const int l = tid & 15;  // lane within the FFT
-  const int64_t nb = min((int64_t)kFBlk, a.n_blocks - b0);
-
+  const int nb = (int)min((int64_t)kFBlk, a.n_blocks - b0);
   // Samples t = l + 16 n2 of block b0 + f (and, filterbank, of block b0 + 16
-  // + f for slots f < TAPS - 1, into wx), inputs i0..i0+IN-1 (zero outside;
-  // a block is read when some output of this workgroup uses it).
+  // + f for slots f < TAPS - 1, into wx), inputs i0..i0+IN-1 (zero outside), at
+  // any alignment.
   uint32_t w[16][kW];
   uint32_t wx[TAPS > 1 ? 16 : 1][kW];
   constexpr int kLoads = TAPS > 1 ? 2 : 1;
 #pragma unroll
   for (int e = 0; e < kLoads; ++e) {
-    const int j = e == 0 ? f : kFBlk + f;            // block offset from b0
     if (e == 1 && f >= TAPS - 1) break;
-    const bool need = j < nb + TAPS - 1;
+    // block offset from b0: past the end the last block again, whose transform
+    // nothing reads (no condition may stand around the loads: they would be
+    // waited for before the next ones)
+    const int j = min(e == 0 ? f : kFBlk + f, nb + TAPS - 2);
     uint32_t v[16][kW];
-    if (a.vec_in && nb == kFBlk) {
+    if (IN != 4 || a.groups == FGroups::kFull) {
       const int8_t* p = a.volt + ((b0 + j) * kFN + l) * a.n_in + i0;
 #pragma unroll
       for (int n2 = 0; n2 < 16; ++n2) {
         const int8_t* q = p + (int64_t)n2 * 16 * a.n_in;
         if constexpr (IN == 16) {
-          const uint4 u = *reinterpret_cast<const uint4*>(q);
+          const uint4 u = load_any<uint4>(q);
           v[n2][0] = u.x; v[n2][1] = u.y; v[n2][2] = u.z; v[n2][3] = u.w;
         } else if constexpr (IN == 8) {
-          const uint2 u = *reinterpret_cast<const uint2*>(q);
+          const uint2 u = load_any<uint2>(q);
           v[n2][0] = u.x; v[n2][1] = u.y;
         } else {
-          v[n2][0] = *reinterpret_cast<const uint32_t*>(q);
+          v[n2][0] = load_any<uint32_t>(q);
         }
       }
-    } else {
+    } else if (a.groups == FGroups::kShift) {
+      // a last input group that is not full is read from the row's last inputs
+      // and shifted down, so that every load stays in its row
+      const int back = max(0, i0 + IN - a.n_in);
+      const int8_t* p = a.volt + ((b0 + j) * kFN + l) * a.n_in + (i0 - back);
 #pragma unroll
       for (int n2 = 0; n2 < 16; ++n2) {
-        const int64_t t = (b0 + j) * kFN + l + 16 * n2;
-        const int8_t* p = a.volt + t * a.n_in + i0;
-#pragma unroll
-        for (int jj = 0; jj < kW; ++jj) {
-          uint32_t u = 0;
-          for (int q = 0; q < 4; ++q) {
-            const int i = 4 * jj + q;
-            if (need && i0 + i < a.n_in) u |= (uint32_t)(uint8_t)p[i] << (8 * q);
-          }
-          v[n2][jj] = u;
-        }
+        const int8_t* q = p + (int64_t)n2 * 16 * a.n_in;
+        v[n2][0] = load_any<uint32_t>(q) >> (8 * back);
+      }
+    } else {
+      for (int n2 = 0; n2 < 16; ++n2) {
+        const int8_t* p = a.volt + ((b0 + j) * kFN + l + 16 * n2) * a.n_in;
+        v[n2][0] = 0;
+        for (int i = 0; i < a.n_in; ++i) v[n2][0] |= (uint32_t)(uint8_t)p[i] << (8 * i);
       }
     }
     if (e == 0) {
@@ -324,9 +329,9 @@ __global__ __launch_bounds__(256, 3) void fstage_kernel(FArgs a) {
 }
 
 // Inputs per workgroup.  A workgroup's time goes with its inputs and the GPU
-// holds 768 at once (512 of 16 inputs), so a call that leaves CUs idle takes
-// fewer inputs per workgroup; a large one takes 16, whose requests fill twice
-// the part of a line.  64 inputs, F-stage to dump, with 16 / 8 / 4 inputs:
+// holds 768 at once, so a call that leaves CUs idle takes fewer inputs per
+// workgroup; a large one takes 16, whose requests fill twice the part of a line.
+// 64 inputs, F-stage to dump, with 16 / 8 / 4 inputs:
 // 100 blocks 62 / 44 / 34 us, 1000 blocks 78 / 61 / 57, 1900 blocks 81 with 8
 // and 75 with 4, 4000 blocks 86 / 84 and from there 16 is level or better.  The
 // filterbank path takes at most 8: 100 blocks 50 us with 8 and 37 with 4, 1900
@@ -337,7 +342,7 @@ hipError_t launch_fstage(const FArgs& a, int taps, hipStream_t s) {
   const int in = (taps == 1 && a.n_in % 16 == 0 && n_bg * (a.n_in / 16) >= 1024) ? 16 : fstage_inputs(n_bg, a.n_in, 1024);
   FArgs b = a;
   b.n_ig = (a.n_in + in - 1) / in;
-  b.vec_in = (a.n_in % in == 0) && ((reinterpret_cast<uintptr_t>(a.volt) & (in - 1)) == 0);
+  b.groups = fstage_groups(a.n_in, in, in);
   b.n_items = (n_bg + 3) / 4 * 4 * b.n_ig;   // block groups padded to whole ring lines
   if (b.n_items <= 0) return hipSuccess;
   b.per_xcd = (b.n_items + kNumXcd - 1) / kNumXcd;

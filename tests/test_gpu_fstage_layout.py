@@ -2,7 +2,7 @@
 size of the call) and input alignment give the same codes.
 
 Each call is compared, bit for bit, with the same blocks given 15 at a time:
-those launches read their samples one by one and have 4 inputs per workgroup.
+those launches have 4 inputs per workgroup and a ragged block group.
 The arithmetic of a block (of a pair of real inputs) does not depend on the
 split, so nothing may differ; the small calls' spectra and codes are held to
 the FP64 transform."""
@@ -40,7 +40,10 @@ def raw_rows(fmt, blocks, n_in):
 CASES = [("r8", 0, 64, 4083), ("r8", 0, 64, 4103), ("r8", 0, 72, 1819), ("r8", 0, 72, 1803), ("r8", 0, 20, 77),
          ("r8", 0, 13, 40), ("r8", 0, 1, 33), ("r8", 4, 64, 2059), ("r8", 4, 64, 2027), ("r8", 4, 12, 50),
          ("r8", 4, 5, 21), ("cw16", 0, 64, 1545), ("cw16", 0, 64, 1519), ("cw16", 0, 12, 45), ("cw16", 0, 3, 18),
-         ("cb8", 0, 64, 1545), ("cb8", 0, 64, 1519), ("cb8", 0, 12, 45), ("cb8", 0, 7, 18)]
+         ("cb8", 0, 64, 1545), ("cb8", 0, 64, 1519), ("cb8", 0, 12, 45), ("cb8", 0, 7, 18),
+         # the last input group reads back into the row; the fewest inputs
+         ("r8", 0, 62, 300), ("r8", 0, 3, 35), ("r8", 4, 1, 18), ("r8", 4, 30, 65), ("cw16", 0, 61, 129),
+         ("cw16", 0, 2, 17), ("cw16", 0, 1, 34), ("cb8", 0, 58, 100), ("cb8", 0, 1, 31), ("cb8", 0, 2, 16)]
 
 
 @pytest.mark.parametrize("fmt,taps,n_in,n_blocks", CASES)
