@@ -255,6 +255,11 @@ __device__ __forceinline__ void mfma_tile(const XArgs& a, int8_t* lds, int ch, i
   // 8*(r/4) + 4*(l/32) + r%4, column l%32.
   float scale = 1.0f;
   if constexpr (EK == kElemF8) scale = a.inv_scale2 ? a.inv_scale2[ch] : 1.0f;
+  auto scaled = [&](auto x) {
+    if constexpr (EK == kElemI8) return x;
+    else return x * scale;
+  };
+  const int64_t out0 = (int64_t)split * a.out_split_stride + (int64_t)ch * a.n_products;
 #pragma unroll
   for (int m = 0; m < MB; ++m)
 #pragma unroll
@@ -262,36 +267,17 @@ __device__ __forceinline__ void mfma_tile(const XArgs& a, int8_t* lds, int ch, i
       if (DIAG && wm == wn && m < n) continue;
       const int j = J * BT + wn * WT + n * 32 + (lane & 31);
 #pragma unroll
-      for (int r = 0; r < 16; ++r) {
-        const int i = I * BT + wm * WT + m * 32 + 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3);
-        if (i < a.n_in && j <= i) {
-          const int64_t off = (int64_t)split * a.out_split_stride + (int64_t)ch * a.n_products + tri_index(i, j);
-          if constexpr (EK == kElemI8) {
-            int2* pp = static_cast<int2*>(a.out) + off;
-            const int re = vr[m][n][r];
-            const int im = (i == j) ? 0 : vi[m][n][r];
-            if (a.accumulate) {
-              int2 o = *pp;
-              o.x += re;
-              o.y += im;
-              *pp = o;
-            } else {
-              *pp = make_int2(re, im);
-            }
-          } else {
-            float2* pp = static_cast<float2*>(a.out) + off;
-            const float re = vr[m][n][r] * scale;
-            const float im = (i == j) ? 0.f : vi[m][n][r] * scale;
-            if (a.accumulate) {
-              float2 o = *pp;
-              o.x += re;
-              o.y += im;
-              *pp = o;
-            } else {
-              *pp = make_float2(re, im);
-            }
-          }
+      for (int h = 0; h < 16; h += 8) {
+        uint32_t off[8];
+        std::conditional_t<std::is_same_v<Acc, v16i>, int2, float2> v[8];
+#pragma unroll
+        for (int r = h; r < h + 8; ++r) {
+          const int i = I * BT + wm * WT + m * 32 + 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3);
+          off[r - h] = i < a.n_in && j <= i ? (uint32_t)tri_index(i, j) : kNoProduct;
+          v[r - h].x = scaled(vr[m][n][r]);
+          v[r - h].y = i == j ? 0 : scaled(vi[m][n][r]);
         }
+        put_products(static_cast<std::remove_reference_t<decltype(v[0])>*>(a.out) + out0, off, v, a.accumulate);
       }
     }
 }
@@ -572,42 +558,28 @@ __device__ __forceinline__ void mfma_tile_128(const XArgs& a, int8_t* lds, int c
   // 8*(r/4) + 4*(l/32) + r%4, column l%32.
   float scale = 1.0f;
   if constexpr (EK == kElemF8) scale = a.inv_scale2 ? a.inv_scale2[ch] : 1.0f;
+  auto scaled = [&](auto x) {
+    if constexpr (EK == kElemI8) return x;
+    else return x * scale;
+  };
+  const int64_t out0 = (int64_t)split * a.out_split_stride + (int64_t)ch * a.n_products;
 #pragma unroll
   for (int m = 0; m < 2; ++m)
 #pragma unroll
     for (int n = 0; n < 2; ++n) {
       const int j = J * BT + wn * 64 + n * 32 + (lane & 31);
 #pragma unroll
-      for (int r = 0; r < 16; ++r) {
-        const int i = I * BT + wm * 64 + m * 32 + 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3);
-        if (i < a.n_in && j <= i) {
-          const int64_t off = (int64_t)split * a.out_split_stride + (int64_t)ch * a.n_products + tri_index(i, j);
-          if constexpr (EK == kElemI8) {
-            int2* pp = static_cast<int2*>(a.out) + off;
-            const int re = vr[m][n][r];
-            const int im = (i == j) ? 0 : vi[m][n][r];
-            if (a.accumulate) {
-              int2 o = *pp;
-              o.x += re;
-              o.y += im;
-              *pp = o;
-            } else {
-              *pp = make_int2(re, im);
-            }
-          } else {
-            float2* pp = static_cast<float2*>(a.out) + off;
-            const float re = vr[m][n][r] * scale;
-            const float im = (i == j) ? 0.f : vi[m][n][r] * scale;
-            if (a.accumulate) {
-              float2 o = *pp;
-              o.x += re;
-              o.y += im;
-              *pp = o;
-            } else {
-              *pp = make_float2(re, im);
-            }
-          }
+      for (int h = 0; h < 16; h += 8) {
+        uint32_t off[8];
+        std::conditional_t<std::is_same_v<Acc, v16i>, int2, float2> v[8];
+#pragma unroll
+        for (int r = h; r < h + 8; ++r) {
+          const int i = I * BT + wm * 64 + m * 32 + 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3);
+          off[r - h] = i < a.n_in && j <= i ? (uint32_t)tri_index(i, j) : kNoProduct;
+          v[r - h].x = scaled(vr[m][n][r]);
+          v[r - h].y = i == j ? 0 : scaled(vi[m][n][r]);
         }
+        put_products(static_cast<std::remove_reference_t<decltype(v[0])>*>(a.out) + out0, off, v, a.accumulate);
       }
     }
 }
@@ -842,6 +814,7 @@ __device__ __forceinline__ void mfma_tile_128_cvt(const XArgs& a, int8_t* lds, i
   // Epilogue (32 x 32 accumulator layout: register r of lane l holds row
   // 8*(r/4) + 4*(l/32) + r%4, column l%32).  FP8 sums are s_c^2 V exactly.
   const float scale = EKM == kElemF8 ? 1.f / (sc * sc) : 1.f;
+  const int64_t out0 = (int64_t)split * a.out_split_stride + (int64_t)ch * a.n_products;
 #pragma unroll
   for (int m = 0; m < 2; ++m)
 #pragma unroll
@@ -849,22 +822,16 @@ __device__ __forceinline__ void mfma_tile_128_cvt(const XArgs& a, int8_t* lds, i
       if (skip(m, n)) continue;
       const int j = J * BT + (wn * NBN + n) * 32 + (lane & 31);
 #pragma unroll
-      for (int r = 0; r < 16; ++r) {
-        const int i = I * BT + wm * 64 + m * 32 + 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3);
-        if (i < a.n_in && j <= i) {
-          const int64_t off = (int64_t)split * a.out_split_stride + (int64_t)ch * a.n_products + tri_index(i, j);
-          float2* pp = static_cast<float2*>(a.out) + off;
-          const float re = vr[m][n][r] * scale;
-          const float im = (i == j) ? 0.f : vi[m][n][r] * scale;
-          if (a.accumulate) {
-            float2 o = *pp;
-            o.x += re;
-            o.y += im;
-            *pp = o;
-          } else {
-            *pp = make_float2(re, im);
-          }
+      for (int h = 0; h < 16; h += 8) {
+        uint32_t off[8];
+        float2 v[8];
+#pragma unroll
+        for (int r = h; r < h + 8; ++r) {
+          const int i = I * BT + wm * 64 + m * 32 + 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3);
+          off[r - h] = i < a.n_in && j <= i ? (uint32_t)tri_index(i, j) : kNoProduct;
+          v[r - h] = make_float2(vr[m][n][r] * scale, i == j ? 0.f : vi[m][n][r] * scale);
         }
+        put_products(static_cast<float2*>(a.out) + out0, off, v, a.accumulate);
       }
     }
 }
@@ -1151,6 +1118,27 @@ __device__ __forceinline__ void mfma_tile_128_i8(const XArgs& a, int8_t* lds, in
 
   // Epilogue.  16 x 16 accumulator layout: register r of lane l holds row
   // 4*(l/16) + r, column l%16.
+  // A later pass of the integration, eight products at a time.
+  if constexpr (!THROUGH) if (a.accumulate) {
+    int2* const sum = static_cast<int2*>(a.out) + (int64_t)split * a.out_split_stride + (int64_t)ch * a.n_products;
+#pragma unroll
+    for (int mn = 0; mn < 16; mn += 2) {
+      int lq = lane;
+      asm volatile("" : "+v"(lq));   // indexes made here, not all at once ahead of the loop over K
+      uint32_t off[8];
+      int2 v[8];
+#pragma unroll
+      for (int q = 0; q < 8; ++q) {
+        const int m = (mn + q / 4) / 4, n = (mn + q / 4) % 4;
+        const int i = I * BT + wm * 64 + m * 16 + 4 * (lq >> 4) + q % 4;
+        const int j = J * BT + wn * 64 + n * 16 + (lq & 15);
+        off[q] = i < a.n_in && j <= i ? (uint32_t)tri_index(i, j) : kNoProduct;
+        v[q] = make_int2(EK == kElemCI4 ? vr[m][n][q % 4] >> 8 : vr[m][n][q % 4], i == j ? 0 : EK == kElemCI4 ? vi[m][n][q % 4] >> 8 : vi[m][n][q % 4]);
+      }
+      add_products(sum, off, v);
+    }
+    return;
+  }
 #pragma unroll
   for (int m = 0; m < 4; ++m)
 #pragma unroll
@@ -1168,11 +1156,6 @@ __device__ __forceinline__ void mfma_tile_128_i8(const XArgs& a, int8_t* lds, in
           if constexpr (THROUGH) {
             __hip_atomic_store(reinterpret_cast<uint64_t*>(pp), (uint64_t)(uint32_t)re | (uint64_t)(uint32_t)im << 32,
                                __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
-          } else if (a.accumulate) {
-            int2 o = *pp;
-            o.x += re;
-            o.y += im;
-            *pp = o;
           } else {
             *pp = make_int2(re, im);
           }
@@ -1361,31 +1344,24 @@ __device__ __forceinline__ void mfma_tile_f32(const XArgs& a, int8_t* lds, int c
   if (wave_idle) return;
   // Epilogue.  16 x 16 accumulator layout: register r of lane l holds row
   // 4*(l/16) + r, column l%16.
+  const int64_t out0 = (int64_t)split * a.out_split_stride + (int64_t)ch * a.n_products;
 #pragma unroll
-  for (int m = 0; m < 2; ++m)
+  for (int m = 0; m < 2; ++m) {
+    uint32_t off[8];
+    float2 v[8];
 #pragma unroll
     for (int n = 0; n < 2; ++n) {
-      if (quad_diag && m < n) continue;
       const int j = J * BT + wn * 32 + n * 16 + (lane & 15);
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
         const int i = I * BT + wm * 32 + m * 16 + 4 * (lane >> 4) + r;
-        if (i < a.n_in && j <= i) {
-          const int64_t off = (int64_t)split * a.out_split_stride + (int64_t)ch * a.n_products + tri_index(i, j);
-          float2* pp = static_cast<float2*>(a.out) + off;
-          const float re = vr[m][n][r];
-          const float im = (i == j) ? 0.f : vi[m][n][r];
-          if (a.accumulate) {
-            float2 o = *pp;
-            o.x += re;
-            o.y += im;
-            *pp = o;
-          } else {
-            *pp = make_float2(re, im);
-          }
-        }
+        off[4 * n + r] =
+            !(quad_diag && m < n) && i < a.n_in && j <= i ? (uint32_t)tri_index(i, j) : kNoProduct;
+        v[4 * n + r] = make_float2(vr[m][n][r], i == j ? 0.f : vi[m][n][r]);
       }
     }
+    put_products(static_cast<float2*>(a.out) + out0, off, v, a.accumulate);
+  }
 }
 
 // Diagonal or off-diagonal tile of the BT-row engine (one instantiation site
