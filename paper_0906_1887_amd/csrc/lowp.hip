@@ -8,39 +8,50 @@
 // [2^-60, 2^60]).  Scaling by a power of two is
 // exact in FP32, so the X-engine epilogue recovers V by multiplying by
 // 1/s_c^2, also exactly.
+#include <algorithm>
+
 #include "common.h"
 #include "launch.h"
 
 namespace corr {
 
+// Lanes of a workgroup that share one row of n units (a power of two, so that
+// short rows of several lie side by side): log2.
+static int lanes_log2(int64_t n) {
+  int l = 0;
+  while (l < 8 && (int64_t(1) << l) < n) ++l;
+  return l;
+}
+
 // Max |re|, |im| per channel (as float bits; non-negative floats order like
 // their bit patterns), one atomicMax per workgroup.  Each lane reads two
-// complex samples (16 bytes, any alignment) at a time.
+// complex samples (16 bytes, any alignment) at a time; 2^row_lanes lanes take a
+// row, so a workgroup has 256 / 2^row_lanes rows at once.  Bound by the read
+// (5.2 TB/s for rows of 4239 samples).  With all 256 lanes on one row at a
+// time and 4 rows per workgroup, 355 x 264 rows of 88 samples took 79 us, and 43
+// to convert; now 41 together.
 __global__ __launch_bounds__(256) void absmax_kernel(const float* __restrict__ x, int64_t n_in, int64_t n_t,
-                                                      int64_t row_stride, int64_t rows_per_wg,
+                                                      int64_t row_stride, int64_t rows_per_wg, int row_lanes,
                                                       uint32_t* __restrict__ m_bits) {
   const int64_t ch = blockIdx.y;
   const int64_t r0 = (int64_t)blockIdx.x * rows_per_wg;
   const int64_t r1 = min(n_in, r0 + rows_per_wg);
   const int tid = threadIdx.x;
+  const int L = 1 << row_lanes;
+  const int lane = tid & (L - 1);
+  auto top = [](float4 a) { return fmaxf(fmaxf(fabsf(a.x), fabsf(a.y)), fmaxf(fabsf(a.z), fabsf(a.w))); };
   float m = 0.f;
-  for (int64_t r = r0; r < r1; ++r) {
+  const int64_t nv = n_t / 2;
+  for (int64_t r = r0 + (tid >> row_lanes); r < r1; r += 256 >> row_lanes) {
     const float* row = x + ((ch * n_in + r) * row_stride) * 2;
-    const int64_t nv = n_t / 2;
-    int64_t u = tid;
-    for (; u + 768 < nv; u += 1024) {
-      const float4 a = load16_any<float4>(row + 4 * u), b = load16_any<float4>(row + 4 * (u + 256));
-      const float4 c = load16_any<float4>(row + 4 * (u + 512)), d = load16_any<float4>(row + 4 * (u + 768));
-      m = fmaxf(m, fmaxf(fmaxf(fmaxf(fabsf(a.x), fabsf(a.y)), fmaxf(fabsf(a.z), fabsf(a.w))),
-                         fmaxf(fmaxf(fabsf(b.x), fabsf(b.y)), fmaxf(fabsf(b.z), fabsf(b.w)))));
-      m = fmaxf(m, fmaxf(fmaxf(fmaxf(fabsf(c.x), fabsf(c.y)), fmaxf(fabsf(c.z), fabsf(c.w))),
-                         fmaxf(fmaxf(fabsf(d.x), fabsf(d.y)), fmaxf(fabsf(d.z), fabsf(d.w)))));
+    int64_t u = lane;
+    for (; u + 3 * L < nv; u += 4 * L) {
+      const float4 a = load16_any<float4>(row + 4 * u), b = load16_any<float4>(row + 4 * (u + L));
+      const float4 c = load16_any<float4>(row + 4 * (u + 2 * L)), d = load16_any<float4>(row + 4 * (u + 3 * L));
+      m = fmaxf(m, fmaxf(fmaxf(top(a), top(b)), fmaxf(top(c), top(d))));
     }
-    for (; u < nv; u += 256) {
-      const float4 a = load16_any<float4>(row + 4 * u);
-      m = fmaxf(m, fmaxf(fmaxf(fabsf(a.x), fabsf(a.y)), fmaxf(fabsf(a.z), fabsf(a.w))));
-    }
-    if ((n_t & 1) && tid == 0) m = fmaxf(m, fmaxf(fabsf(row[2 * n_t - 2]), fabsf(row[2 * n_t - 1])));
+    for (; u < nv; u += L) m = fmaxf(m, top(load16_any<float4>(row + 4 * u)));
+    if ((n_t & 1) && lane == 0) m = fmaxf(m, fmaxf(fabsf(row[2 * n_t - 2]), fabsf(row[2 * n_t - 1])));
   }
   __shared__ float red[256];
   red[tid] = m;
@@ -53,22 +64,23 @@ __global__ __launch_bounds__(256) void absmax_kernel(const float* __restrict__ x
 }
 
 // One thread converts 4 complex samples of one row (grid: sample groups x
-// rows x channels).  Out rows have out_stride samples; FP16: 4 bytes per
+// rows x channels; 2^row_lanes lanes take a row, so a workgroup has 256 /
+// 2^row_lanes rows).  Out rows have out_stride samples; FP16: 4 bytes per
 // sample, FP8: 2.  Full groups are read as two 16-byte loads of any alignment.
 template <int ELEM>
 __global__ __launch_bounds__(256) void lowp_convert_kernel(const float* __restrict__ x, int64_t n_in, int64_t n_t,
                                                            int64_t row_stride, int64_t out_stride,
-                                                           const uint32_t* __restrict__ m_bits, void* __restrict__ out,
+                                                           int row_lanes, const uint32_t* __restrict__ m_bits, void* __restrict__ out,
                                                            float* __restrict__ inv_scale2) {
   const int64_t ch = blockIdx.z;
-  const int64_t r = blockIdx.y;
-  const int64_t t0 = 4 * ((int64_t)blockIdx.x * 256 + threadIdx.x);
+  const int64_t r = ((int64_t)blockIdx.y << (8 - row_lanes)) + (threadIdx.x >> row_lanes);
+  const int64_t t0 = 4 * (((int64_t)blockIdx.x << row_lanes) + (threadIdx.x & ((1 << row_lanes) - 1)));
   float s = 1.f;
   if (ELEM == kElemF8) {
     s = e4m3_scale(__uint_as_float(m_bits[ch]));
     if (r == 0 && t0 == 0) inv_scale2[ch] = 1.f / (s * s);
   }
-  if (t0 >= n_t) return;
+  if (t0 >= n_t || r >= n_in) return;
   const float* src = x + ((ch * n_in + r) * row_stride + t0) * 2;
   float v[8];
   if (t0 + 4 <= n_t) {
@@ -118,9 +130,13 @@ hipError_t launch_absmax(const float* x, int64_t n_ch, int64_t n_in, int64_t n_t
   if (n_ch > 65535) return hipErrorInvalidValue;
   hipError_t e = launch_fill_zero(m_bits, (n_ch * 4 + 15) / 16 * 16, s);
   if (e != hipSuccess || n_t <= 0) return e;
-  const int64_t rows_per_wg = 4;
+  // rows of 32 KB, at least 4 and one for each group of lanes (256 KB left too few
+  // workgroups: 192 inputs x 11 channels x 526 samples 220 us a pass instead of
+  // 120; 16 KB was level but for 64 x 512 x 512, 86 against 82 us)
+  const int row_lanes = lanes_log2((n_t + 1) / 2);
+  const int64_t rows_per_wg = std::max<int64_t>({4, 4096 / std::max<int64_t>(1, n_t), 256 >> row_lanes});
   const dim3 g((unsigned)((n_in + rows_per_wg - 1) / rows_per_wg), (unsigned)n_ch);
-  hipLaunchKernelGGL(absmax_kernel, g, dim3(256), 0, s, x, n_in, n_t, row_stride, rows_per_wg, m_bits);
+  hipLaunchKernelGGL(absmax_kernel, g, dim3(256), 0, s, x, n_in, n_t, row_stride, rows_per_wg, row_lanes, m_bits);
   return hipGetLastError();
 }
 
@@ -131,12 +147,14 @@ hipError_t launch_lowp_stage(const LowpCall& c, hipStream_t s) {
     const hipError_t e = launch_absmax(c.x, c.n_ch, c.n_in, c.n_t, c.row_stride, c.m_bits, s);
     if (e != hipSuccess) return e;
   }
+  const int row_lanes = lanes_log2((c.n_t + 3) / 4);
   const int64_t gx = ((c.n_t + 3) / 4 + 255) / 256;
+  const int64_t gy = ((int64_t)c.n_in + (255 >> row_lanes)) >> (8 - row_lanes);
   if (gx > 0x7FFFFFFF) return hipErrorInvalidValue;
-  const dim3 g((unsigned)gx, (unsigned)c.n_in, (unsigned)c.n_ch);
+  const dim3 g((unsigned)gx, (unsigned)gy, (unsigned)c.n_ch);
 #define CORR_CONVERT(EL)                                                                                      \
   hipLaunchKernelGGL((lowp_convert_kernel<EL>), g, dim3(256), 0, s, c.x, (int64_t)c.n_in, c.n_t, c.row_stride, \
-                     c.out_stride, c.m_bits, c.out, c.inv_scale2)
+                     c.out_stride, row_lanes, c.m_bits, c.out, c.inv_scale2)
   if (c.elem == kElemF16) {
     CORR_CONVERT(kElemF16);
   } else {
