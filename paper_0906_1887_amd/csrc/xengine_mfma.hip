@@ -72,10 +72,36 @@ __device__ __forceinline__ v4i rot4(v4i v) {
   return r;
 }
 
+// CI4 samples (one byte per complex sample: re in bits 7..4, im in bits 3..0,
+// two's complement nibbles, the "1-byte" mode of Sec. 5) are unpacked in
+// registers into int8 operands scaled by 16: the byte's high nibble with the
+// low nibble cleared is 16 re, and the low nibble shifted up is 16 im, both
+// exact in int8 for |re|, |im| <= 7.  Operand bytes run [16 re of 4 samples,
+// 16 im of the same 4, 16 re of the next 4, 16 im of those]; the same order
+// in A and B makes A B^T = sum (re re' + im im') = Re V (times 256).
+constexpr uint32_t kHiNib = 0xF0F0F0F0u;
+__device__ __forceinline__ v4i ci4_plain(int w0, int w1) {
+  const uint32_t u0 = (uint32_t)w0, u1 = (uint32_t)w1;
+  return v4i{(int)(u0 & kHiNib), (int)((u0 << 4) & kHiNib), (int)(u1 & kHiNib), (int)((u1 << 4) & kHiNib)};
+}
+// -16 re per byte of a high-nibble word: flip the nibble and add 1 in it; a
+// carry out of a byte (re = 0) lands in the next byte's clear low nibble and
+// is masked off.
+__device__ __forceinline__ uint32_t neg_hi_nibbles(uint32_t x) { return ((x ^ kHiNib) + 0x10101010u) & kHiNib; }
+// Operands of -iA = (im, -re) in the same byte order: A' B^T = sum (im re' -
+// re im') = Im V (times 256).
+__device__ __forceinline__ v4i ci4_rotm(int w0, int w1) {
+  const uint32_t u0 = (uint32_t)w0, u1 = (uint32_t)w1;
+  return v4i{(int)((u0 << 4) & kHiNib), (int)neg_hi_nibbles(u0 & kHiNib), (int)((u1 << 4) & kHiNib),
+             (int)neg_hi_nibbles(u1 & kHiNib)};
+}
+
 template <int EK>
 struct MAcc;
 template <>
 struct MAcc<kElemI8> { typedef v16i T; };
+template <>
+struct MAcc<kElemCI4> { typedef v16i T; };
 template <>
 struct MAcc<kElemF16> { typedef v16f T; };
 template <>
@@ -99,6 +125,21 @@ __device__ __forceinline__ void mfma64(const v4i (&a)[2], const v4i (&b)[2], typ
     // format 0 (FP8 E4M3) for both operands, unit E8M0 scales (127 = 2^0)
     acc = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(a8, b8, acc, 0, 0, 0, 127, 0, 127);
   }
+}
+
+// The same of packed CI4 samples: each read holds 16, of two K halves.  Up to 64
+// inputs in 64-row tiles: 32 x 90 channels x 7109 samples to dump 36 us, 60 in
+// 128-row tiles (16 times the products that are stored); 64 x 512 x 4000 54 and
+// 115.
+__device__ __forceinline__ void mfma64_ci4(const v4i (&a)[2], const v4i (&b)[2], v16i& vr, v16i& vi) {
+#pragma unroll
+  for (int h = 0; h < 2; ++h)
+#pragma unroll
+    for (int q = 0; q < 4; q += 2) {
+      const v4i bp = ci4_plain(b[h][q], b[h][q + 1]);
+      vr = __builtin_amdgcn_mfma_i32_32x32x32_i8(ci4_plain(a[h][q], a[h][q + 1]), bp, vr, 0, 0, 0);
+      vi = __builtin_amdgcn_mfma_i32_32x32x32_i8(ci4_rotm(a[h][q], a[h][q + 1]), bp, vi, 0, 0, 0);
+    }
 }
 
 template <int N>
@@ -236,7 +277,7 @@ __device__ __forceinline__ void mfma_tile(const XArgs& a, int8_t* lds, int ch, i
         for (int n = 0; n < MB; ++n) {
           const int r = wn * WT + n * 32 + frow;
           bf[n][h] = *reinterpret_cast<const v4i*>(Bs + r * kMKC + 16 * (cidx ^ swz(r)));
-          bj[n][h] = rot4<EK>(bf[n][h]);
+          if constexpr (EK != kElemCI4) bj[n][h] = rot4<EK>(bf[n][h]);
         }
       }
 #pragma unroll
@@ -244,8 +285,12 @@ __device__ __forceinline__ void mfma_tile(const XArgs& a, int8_t* lds, int ch, i
 #pragma unroll
         for (int n = 0; n < MB; ++n) {
           if (DIAG && wm == wn && m < n) continue;   // strictly upper 32 x 32 block
-          mfma64<EK>(af[m], bf[n], vr[m][n]);
-          mfma64<EK>(af[m], bj[n], vi[m][n]);
+          if constexpr (EK == kElemCI4) {
+            mfma64_ci4(af[m], bf[n], vr[m][n], vi[m][n]);
+          } else {
+            mfma64<EK>(af[m], bf[n], vr[m][n]);
+            mfma64<EK>(af[m], bj[n], vi[m][n]);
+          }
         }
     }
   }
@@ -257,6 +302,7 @@ __device__ __forceinline__ void mfma_tile(const XArgs& a, int8_t* lds, int ch, i
   if constexpr (EK == kElemF8) scale = a.inv_scale2 ? a.inv_scale2[ch] : 1.0f;
   auto scaled = [&](auto x) {
     if constexpr (EK == kElemI8) return x;
+    else if constexpr (EK == kElemCI4) return x >> 8;   // the operands are 16 x the sample parts
     else return x * scale;
   };
   const int64_t out0 = (int64_t)split * a.out_split_stride + (int64_t)ch * a.n_products;
@@ -834,30 +880,6 @@ __device__ __forceinline__ void mfma_tile_128_cvt(const XArgs& a, int8_t* lds, i
         put_products(static_cast<float2*>(a.out) + out0, off, v, a.accumulate);
       }
     }
-}
-
-// CI4 samples (one byte per complex sample: re in bits 7..4, im in bits 3..0,
-// two's complement nibbles, the "1-byte" mode of Sec. 5) are unpacked in
-// registers into int8 operands scaled by 16: the byte's high nibble with the
-// low nibble cleared is 16 re, and the low nibble shifted up is 16 im, both
-// exact in int8 for |re|, |im| <= 7.  Operand bytes run [16 re of 4 samples,
-// 16 im of the same 4, 16 re of the next 4, 16 im of those]; the same order
-// in A and B makes A B^T = sum (re re' + im im') = Re V (times 256).
-constexpr uint32_t kHiNib = 0xF0F0F0F0u;
-__device__ __forceinline__ v4i ci4_plain(int w0, int w1) {
-  const uint32_t u0 = (uint32_t)w0, u1 = (uint32_t)w1;
-  return v4i{(int)(u0 & kHiNib), (int)((u0 << 4) & kHiNib), (int)(u1 & kHiNib), (int)((u1 << 4) & kHiNib)};
-}
-// -16 re per byte of a high-nibble word: flip the nibble and add 1 in it; a
-// carry out of a byte (re = 0) lands in the next byte's clear low nibble and
-// is masked off.
-__device__ __forceinline__ uint32_t neg_hi_nibbles(uint32_t x) { return ((x ^ kHiNib) + 0x10101010u) & kHiNib; }
-// Operands of -iA = (im, -re) in the same byte order: A' B^T = sum (im re' -
-// re im') = Im V (times 256).
-__device__ __forceinline__ v4i ci4_rotm(int w0, int w1) {
-  const uint32_t u0 = (uint32_t)w0, u1 = (uint32_t)w1;
-  return v4i{(int)((u0 << 4) & kHiNib), (int)neg_hi_nibbles(u0 & kHiNib), (int)((u1 << 4) & kHiNib),
-             (int)neg_hi_nibbles(u1 & kHiNib)};
 }
 
 // int8 variant of mfma_tile_128 on v_mfma_i32_16x16x64_i8: the same staging,
@@ -1623,7 +1645,7 @@ hipError_t launch_xeng_mfma(const XArgs& a, int elem, int bt, hipStream_t s) {
   } else if (elem == kElemF32) {
     CORR_LAUNCH(kElemF32, 64);   // 64-row tiles only
   } else if (elem == kElemCI4) {
-    CORR_LAUNCH_W2(kElemCI4);   // 128-row tiles only
+    if (bt == 128) CORR_LAUNCH_W2(kElemCI4); else CORR_LAUNCH(kElemCI4, 64);
   } else if (elem == kElemF16Cvt) {   // 128-row tiles only
     hipLaunchKernelGGL((xeng_cvt_128_kernel<kElemF16Cvt>), g, dim3(cvt_waves<kElemF16Cvt>() * 64), 0, s, a);
   } else if (elem == kElemF8Cvt) {
