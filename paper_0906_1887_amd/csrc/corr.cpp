@@ -112,12 +112,10 @@ int max_split_of(int64_t items) {
 Layout layout_of(const corr_config* c) {
   Layout L;
   L.n_products = n_products(c->n_inputs);
-  // The converting FP16/FP8 engines run 128-row tiles only; the FP32
-  // engines 64-row tiles only (on the vector ALUs 128-row ones were level where
+  // The FP32 engines run 64-row tiles only (on the vector ALUs 128-row ones were level where
   // they fill the GPU, and up to 1.4 times slower where they pad or leave CUs idle)
-  const bool lowp_cvt = (c->engine == CORR_X_F16 || c->engine == CORR_X_F8) && c->ring_samples == 0;
   const bool fp32 = c->engine == CORR_X_FP32 || c->engine == CORR_X_FP32M;
-  L.bt = !fp32 && (c->n_inputs > 64 || lowp_cvt) ? 128 : 64;
+  L.bt = !fp32 && c->n_inputs > 64 ? 128 : 64;
   const int64_t nb = (c->n_inputs + L.bt - 1) / L.bt;
   L.n_tiles = (int)(nb * (nb + 1) / 2);
   L.acc_bytes = (size_t)c->n_channels * L.n_products * 8;   // int2 (int8 engine) or float2 (others)

@@ -640,9 +640,23 @@ __device__ __forceinline__ void mfma_tile_128(const XArgs& a, int8_t* lds, int c
 // written to LDS in the staged engine's swizzled layout (8 bytes for FP16, 4
 // for FP8).  The MFMA stage is that of mfma_tile_128, so the sums are those
 // of the staged engine on the same codes.  Two LDS stage buffers, one
-// barrier per stage, one workgroup per CU (the register prefetch takes the
-// room of a second; cvt_waves below sets its wave count).  Samples past the
+// barrier per stage, one 128-row workgroup per CU (the register prefetch takes
+// the room of a second; cvt_waves below sets its wave count).  Samples past the
 // pass are zero; rows past N_I are read from a clamped row and never stored.
+//
+// Up to 64 inputs run 64-row tiles (32 x 32 per wave), 4 (FP16) or 3 (FP8)
+// workgroups per CU, where the 128-row tile loaded and converted its 64 or more
+// missing rows too: 16 inputs x 674 channels x 1063 samples to dump 148 -> 43 us
+// (FP16), 32 x 512 x 2000 172 -> 60, 64 x 512 x 2000 216 -> 130 (4.4 TB/s of
+// samples); FP8 15 x 102 x 1814 76 -> 41, 64 x 512 x 2000 293 -> 215 with its pass
+// for the maximum.
+//
+// With one tile per channel the steady loop has no condition around its loads,
+// so that the compiler waits for the oldest stage only (with one it waits for
+// every load in flight: 64 inputs as above 216 -> 155 us by this alone, 128 x 512 x
+// 2000 303 -> 279).  With several tiles it gains nothing: they drift apart and
+// miss the rows that they share in L2 (4.9 -> 8.1 GB from memory for 256 x 512 x
+// 4096).
 constexpr int kPF = 3;   // stages of float32 samples in flight per workgroup (FP8; FP16 takes 4)
 
 // Two floats -> two binary16 (round to nearest even), the first in the low half.
@@ -654,14 +668,14 @@ __device__ __forceinline__ uint32_t pack_f16x2(float lo, float hi) {
 // part of the tile (32 x 32 blocks 2 x NBN).  In a diagonal tile a block whose
 // columns lie above its rows is skipped, and a wave with no block left only
 // converts and keeps the barriers.
-template <int EK, bool DIAG, int NW>
-__device__ __forceinline__ void mfma_tile_128_cvt(const XArgs& a, int8_t* lds, int ch, int split, int I, int J) {
+template <int EK, int BT, bool DIAG, int NW>
+__device__ __forceinline__ void mfma_tile_cvt(const XArgs& a, int8_t* lds, int ch, int split, int I, int J) {
   constexpr int EKM = EK == kElemF16Cvt ? kElemF16 : kElemF8;   // the MFMA stage's element kind
   static_assert(NW == 4 || NW == 8, "4 or 8 waves");
   constexpr int NT = NW * 64;                     // threads
   constexpr int NWN = NW / 2;                     // waves across the tile's columns
-  constexpr int NBN = 4 / NWN;                    // 32-column blocks per wave
-  constexpr int BT = 128;
+  constexpr int NBN = BT / 32 / NWN;              // 32-column blocks per wave
+  constexpr int MB = BT / 64;                     // 32-row blocks per wave
   constexpr int PANEL = BT * kMKC;                // bytes per operand per stage
   constexpr int STAGE = PANEL * (DIAG ? 1 : 2);
   constexpr int NOP = DIAG ? 1 : 2;
@@ -726,6 +740,14 @@ __device__ __forceinline__ void mfma_tile_128_cvt(const XArgs& a, int8_t* lds, i
         R[sl][o][q] = v;
       }
   };
+  auto gload_full = [&](auto S, int st) {   // st < n_full
+    constexpr int sl = decltype(S)::value;
+    const int64_t tb = t0 + (int64_t)st * SPS;
+#pragma unroll
+    for (int o = 0; o < NOP; ++o)
+#pragma unroll
+      for (int q = 0; q < L; ++q) R[sl][o][q] = load16_any<float4>(src[o][q] + (tb + 2 * q_f[q]) * 2);
+  };
   auto cvt_store = [&](auto S, int buf) {
     constexpr int sl = decltype(S)::value;
     int8_t* base = lds + buf * STAGE;
@@ -745,9 +767,9 @@ __device__ __forceinline__ void mfma_tile_128_cvt(const XArgs& a, int8_t* lds, i
       }
   };
 
-  Acc vr[2][NBN], vi[2][NBN];
+  Acc vr[MB][NBN], vi[MB][NBN];
 #pragma unroll
-  for (int m = 0; m < 2; ++m)
+  for (int m = 0; m < MB; ++m)
 #pragma unroll
     for (int n = 0; n < NBN; ++n)
 #pragma unroll
@@ -758,15 +780,15 @@ __device__ __forceinline__ void mfma_tile_128_cvt(const XArgs& a, int8_t* lds, i
 
   const int frow = lane & 31;
   const int g = lane >> 5;
-  auto read = [&](int buf, v4i (&af)[2][2], v4i (&bf)[NBN][2]) {
+  auto read = [&](int buf, v4i (&af)[MB][2], v4i (&bf)[NBN][2]) {
     const int8_t* As = lds + buf * STAGE;
     const int8_t* Bs = DIAG ? As : As + PANEL;
 #pragma unroll
     for (int h = 0; h < 2; ++h) {
       const int cidx = 2 * h + g;
 #pragma unroll
-      for (int m = 0; m < 2; ++m) {
-        const int r = wm * 64 + m * 32 + frow;
+      for (int m = 0; m < MB; ++m) {
+        const int r = wm * (BT / 2) + m * 32 + frow;
         af[m][h] = *reinterpret_cast<const v4i*>(As + r * kMKC + 16 * (cidx ^ swz(r)));
       }
 #pragma unroll
@@ -776,24 +798,25 @@ __device__ __forceinline__ void mfma_tile_128_cvt(const XArgs& a, int8_t* lds, i
       }
     }
   };
-  // 32 x 32 block (m, n) of this wave: rows 2 wm + m, columns wn NBN + n (in
+  // 32 x 32 block (m, n) of this wave: rows MB wm + m, columns wn NBN + n (in
   // blocks); above the diagonal of a diagonal tile it is skipped.
-  auto skip = [&](int m, int n) { return DIAG && wn * NBN + n > 2 * wm + m; };
-  const bool idle = DIAG && wn * NBN > 2 * wm + 1;   // every block of the wave skipped
-  auto compute = [&](const v4i (&af)[2][2], const v4i (&bf)[NBN][2]) {
-    v4i ra[2][2];
+  auto skip = [&](int m, int n) { return DIAG && wn * NBN + n > MB * wm + m; };
+  // every block of the wave skipped, or past the last input
+  const bool idle = (DIAG && wn * NBN > MB * wm + MB - 1) || I * BT + wm * (BT / 2) >= a.n_in || J * BT + wn * NBN * 32 >= a.n_in;
+  auto compute = [&](const v4i (&af)[MB][2], const v4i (&bf)[NBN][2]) {
+    v4i ra[MB][2];
     if constexpr (EKM == kElemF8) {
 #pragma unroll
-      for (int m = 0; m < 2; ++m)
+      for (int m = 0; m < MB; ++m)
 #pragma unroll
         for (int n = 0; n < NBN; ++n)
           if (!skip(m, n)) mfma64<EKM>(af[m], bf[n], vr[m][n]);
 #pragma unroll
-      for (int m = 0; m < 2; ++m)
+      for (int m = 0; m < MB; ++m)
 #pragma unroll
         for (int h = 0; h < 2; ++h) ra[m][h] = rotm4<EKM>(af[m][h]);
 #pragma unroll
-      for (int m = 0; m < 2; ++m)
+      for (int m = 0; m < MB; ++m)
 #pragma unroll
         for (int n = 0; n < NBN; ++n)
           if (!skip(m, n)) mfma64<EKM>(ra[m], bf[n], vi[m][n]);
@@ -801,18 +824,18 @@ __device__ __forceinline__ void mfma_tile_128_cvt(const XArgs& a, int8_t* lds, i
 #pragma unroll
       for (int h = 0; h < 2; ++h)
 #pragma unroll
-        for (int m = 0; m < 2; ++m)
+        for (int m = 0; m < MB; ++m)
 #pragma unroll
           for (int n = 0; n < NBN; ++n)
             if (!skip(m, n)) mfma16<EKM>(af[m][h], bf[n][h], vr[m][n]);
 #pragma unroll
-      for (int m = 0; m < 2; ++m)
+      for (int m = 0; m < MB; ++m)
 #pragma unroll
         for (int h = 0; h < 2; ++h) ra[m][h] = rotm4<EKM>(af[m][h]);
 #pragma unroll
       for (int h = 0; h < 2; ++h)
 #pragma unroll
-        for (int m = 0; m < 2; ++m)
+        for (int m = 0; m < MB; ++m)
 #pragma unroll
           for (int n = 0; n < NBN; ++n)
             if (!skip(m, n)) mfma16<EKM>(ra[m][h], bf[n][h], vi[m][n]);
@@ -820,41 +843,62 @@ __device__ __forceinline__ void mfma_tile_128_cvt(const XArgs& a, int8_t* lds, i
   };
 
   using S0 = std::integral_constant<int, 0>;
+  const int n_full = (int)((t1 - t0) / SPS);       // stages whose samples are all there
+  const bool deep = DIAG && a.n_tiles == 1 && n_full > PF + 1;
   static_assert(PF == 3 || PF == 4, "the prologue and the unrolled main loop below are written for 3 or 4 slots");
   // prologue: stages 0 .. PF - 1 in flight (slot p holds stage p)
-  if (0 < n_st) gload(S0{}, 0);
-  if (1 < n_st) gload(std::integral_constant<int, 1>{}, 1);
-  if (2 < n_st) gload(std::integral_constant<int, 2>{}, 2);
-  if constexpr (PF == 4) {
-    if (3 < n_st) gload(std::integral_constant<int, PF == 4 ? 3 : 0>{}, 3);
-  }
-  if (n_st > 0) {
+  if (deep) {
+    gload_full(S0{}, 0);
+    gload_full(std::integral_constant<int, 1>{}, 1);
+    gload_full(std::integral_constant<int, 2>{}, 2);
+    if constexpr (PF == 4) gload_full(std::integral_constant<int, PF == 4 ? 3 : 0>{}, 3);
     cvt_store(S0{}, 0);
-    if (PF < n_st) gload(S0{}, PF);
+    gload_full(S0{}, PF);
+  } else {
+    if (0 < n_st) gload(S0{}, 0);
+    if (1 < n_st) gload(std::integral_constant<int, 1>{}, 1);
+    if (2 < n_st) gload(std::integral_constant<int, 2>{}, 2);
+    if constexpr (PF == 4) {
+      if (3 < n_st) gload(std::integral_constant<int, PF == 4 ? 3 : 0>{}, 3);
+    }
+    if (n_st > 0) {
+      cvt_store(S0{}, 0);
+      if (PF < n_st) gload(S0{}, PF);
+    }
   }
+  // This wave's LDS accesses are done, then every wave's (loads stay in flight).
+  auto barrier = [&] { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); };
   __syncthreads();
   // Stage st lives in register slot st % PF; iteration st converts stage
   // st + 1 (freeing its slot) and refills that slot with stage st + 1 + PF.
-  auto step = [&](auto U, int st) {
+  auto step = [&](auto full, auto U, int st) {
+    constexpr bool FULL = decltype(full)::value;
     constexpr int u = decltype(U)::value;
     constexpr int nx = (u + 1) % PF;
-    v4i af[2][2], bf[NBN][2];
+    v4i af[MB][2], bf[NBN][2];
     if (!idle) read(st & 1, af, bf);
-    if (st + 1 < n_st) {
+    if (FULL || st + 1 < n_st) {
       cvt_store(std::integral_constant<int, nx>{}, (st + 1) & 1);   // the buffer last read in stage st - 1
-      if (st + 1 + PF < n_st) gload(std::integral_constant<int, nx>{}, st + 1 + PF);
+      if constexpr (FULL) gload_full(std::integral_constant<int, nx>{}, st + 1 + PF);
+      else if (st + 1 + PF < n_st) gload(std::integral_constant<int, nx>{}, st + 1 + PF);
     }
     if (!idle) compute(af, bf);
-    __syncthreads();
+    if constexpr (FULL) barrier();
+    else __syncthreads();
   };
-  for (int st0 = 0; st0 < n_st; st0 += PF) {
-    step(std::integral_constant<int, 0>{}, st0);
-    if (st0 + 1 < n_st) step(std::integral_constant<int, 1>{}, st0 + 1);
-    if (st0 + 2 < n_st) step(std::integral_constant<int, 2>{}, st0 + 2);
+  auto steps = [&](auto full, int st) {
+    constexpr bool FULL = decltype(full)::value;
+    step(full, std::integral_constant<int, 0>{}, st);
+    if (FULL || st + 1 < n_st) step(full, std::integral_constant<int, 1>{}, st + 1);
+    if (FULL || st + 2 < n_st) step(full, std::integral_constant<int, 2>{}, st + 2);
     if constexpr (PF == 4) {
-      if (st0 + 3 < n_st) step(std::integral_constant<int, PF == 4 ? 3 : 0>{}, st0 + 3);
+      if (FULL || st + 3 < n_st) step(full, std::integral_constant<int, PF == 4 ? 3 : 0>{}, st + 3);
     }
-  }
+  };
+  int st0 = 0;
+  if (deep)
+    for (; st0 + 2 * PF < n_full; st0 += PF) steps(std::true_type{}, st0);
+  for (; st0 < n_st; st0 += PF) steps(std::false_type{}, st0);
   if (idle) return;
 
   // Epilogue (32 x 32 accumulator layout: register r of lane l holds row
@@ -862,7 +906,7 @@ __device__ __forceinline__ void mfma_tile_128_cvt(const XArgs& a, int8_t* lds, i
   const float scale = EKM == kElemF8 ? 1.f / (sc * sc) : 1.f;
   const int64_t out0 = (int64_t)split * a.out_split_stride + (int64_t)ch * a.n_products;
 #pragma unroll
-  for (int m = 0; m < 2; ++m)
+  for (int m = 0; m < MB; ++m)
 #pragma unroll
     for (int n = 0; n < NBN; ++n) {
       if (skip(m, n)) continue;
@@ -873,7 +917,7 @@ __device__ __forceinline__ void mfma_tile_128_cvt(const XArgs& a, int8_t* lds, i
         float2 v[8];
 #pragma unroll
         for (int r = h; r < h + 8; ++r) {
-          const int i = I * BT + wm * 64 + m * 32 + 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3);
+          const int i = I * BT + wm * (BT / 2) + m * 32 + 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3);
           off[r - h] = i < a.n_in && j <= i ? (uint32_t)tri_index(i, j) : kNoProduct;
           v[r - h] = make_float2(vr[m][n][r] * scale, i == j ? 0.f : vi[m][n][r] * scale);
         }
@@ -1218,8 +1262,20 @@ __global__ __launch_bounds__(cvt_waves<EK>() * 64, 1) void xeng_cvt_128_kernel(X
   if (slot >= a.per_xcd || item >= a.n_items) return;
   int ch, split, I, J;
   item_decode(a, item, ch, split, I, J);
-  if (I == J) mfma_tile_128_cvt<EK, true, cvt_waves<EK>()>(a, lds, ch, split, I, J);
-  else mfma_tile_128_cvt<EK, false, cvt_waves<EK>()>(a, lds, ch, split, I, J);
+  if (I == J) mfma_tile_cvt<EK, 128, true, cvt_waves<EK>()>(a, lds, ch, split, I, J);
+  else mfma_tile_cvt<EK, 128, false, cvt_waves<EK>()>(a, lds, ch, split, I, J);
+}
+
+// Up to 64 inputs: one 64-row tile per channel.
+template <int EK>
+__global__ __launch_bounds__(256, EK == kElemF16Cvt ? 4 : 3) void xeng_cvt_64_kernel(XArgs a) {
+  __shared__ __attribute__((aligned(1024))) int8_t lds[2 * 64 * kMKC];
+  const int64_t slot = blockIdx.x / kNumXcd;
+  const int64_t item = xcd_item(blockIdx.x, a.per_xcd);
+  if (slot >= a.per_xcd || item >= a.n_items) return;
+  int ch, split, I, J;
+  item_decode(a, item, ch, split, I, J);
+  mfma_tile_cvt<EK, 64, true, 4>(a, lds, ch, split, I, J);
 }
 
 // FP32 matrix-core tile: the 64-row tile of mfma_tile (same staging,
@@ -1646,7 +1702,11 @@ hipError_t launch_xeng_mfma(const XArgs& a, int elem, int bt, hipStream_t s) {
     CORR_LAUNCH(kElemF32, 64);   // 64-row tiles only
   } else if (elem == kElemCI4) {
     if (bt == 128) CORR_LAUNCH_W2(kElemCI4); else CORR_LAUNCH(kElemCI4, 64);
-  } else if (elem == kElemF16Cvt) {   // 128-row tiles only
+  } else if (elem == kElemF16Cvt && bt == 64) {
+    hipLaunchKernelGGL((xeng_cvt_64_kernel<kElemF16Cvt>), g, b, 0, s, a);
+  } else if (elem == kElemF8Cvt && bt == 64) {
+    hipLaunchKernelGGL((xeng_cvt_64_kernel<kElemF8Cvt>), g, b, 0, s, a);
+  } else if (elem == kElemF16Cvt) {
     hipLaunchKernelGGL((xeng_cvt_128_kernel<kElemF16Cvt>), g, dim3(cvt_waves<kElemF16Cvt>() * 64), 0, s, a);
   } else if (elem == kElemF8Cvt) {
     hipLaunchKernelGGL((xeng_cvt_128_kernel<kElemF8Cvt>), g, dim3(cvt_waves<kElemF8Cvt>() * 64), 0, s, a);
