@@ -52,6 +52,7 @@ struct Layout {
   int64_t ring_stride = 0;
   int64_t n_products = 0;
   corr::GuardList guards{};            // a guard band after each region
+  int f32_sub = 64;                    // plain FP32: rows a channel has in a panel (64, or a group of channels': 32, 16)
   size_t status = 0;                   // 256 bytes: the guard check's result word
 };
 
@@ -112,17 +113,23 @@ int max_split_of(int64_t items) {
 Layout layout_of(const corr_config* c) {
   Layout L;
   L.n_products = n_products(c->n_inputs);
-  // The FP32 engines run 64-row tiles only (on the vector ALUs 128-row ones were level where
-  // they fill the GPU, and up to 1.4 times slower where they pad or leave CUs idle)
+  // The FP32 engines run 64-row tiles only (on the vector ALUs 128-row ones were
+  // level where they fill the GPU, and up to 1.4 times slower where they pad or
+  // leave CUs idle)
   const bool fp32 = c->engine == CORR_X_FP32 || c->engine == CORR_X_FP32M;
   L.bt = !fp32 && c->n_inputs > 64 ? 128 : 64;
   const int64_t nb = (c->n_inputs + L.bt - 1) / L.bt;
   L.n_tiles = (int)(nb * (nb + 1) / 2);
   L.acc_bytes = (size_t)c->n_channels * L.n_products * 8;   // int2 (int8 engine) or float2 (others)
   if (c->engine == CORR_X_FP32) {
-    // diagonal tiles in pairs; splits up to 8 items per CU while their partials
+    // diagonal tiles in pairs, small ones by 4 or 8 channels; splits up to 8 items per CU while their partials
     // fit corr_correlate_static's array (64 MiB are about 2000 items' products)
-    L.items = ((int64_t)c->n_channels * nb + 1) / 2 + (int64_t)c->n_channels * (L.n_tiles - nb);
+    if (c->n_inputs <= 32) {   // (never slower: fewer items only leave room for more splits)
+      L.f32_sub = c->n_inputs <= 16 ? 16 : 32;
+      L.items = ((int64_t)c->n_channels * L.f32_sub + 127) / 128;
+    } else {
+      L.items = ((int64_t)c->n_channels * nb + 1) / 2 + (int64_t)c->n_channels * (L.n_tiles - nb);
+    }
     const int64_t fit = (int64_t)(CORR_STATIC_SCRATCH_BYTES / L.acc_bytes);
     L.max_split = (int)std::max<int64_t>(corr_internal_static_split(c, INT64_MAX / 2),
                                          std::min<int64_t>({kMaxSplit, (2048 + L.items - 1) / L.items, fit}));
@@ -423,7 +430,7 @@ corr_status corr_internal_xengine(const corr_xpass* q) {
     e = aligned ? corr::launch_xeng_mfma(a, corr::kElemI8, L.bt, q->stream)
                 : corr::launch_xeng_i8u(a, L.bt, q->stream);
   else
-    e = corr::launch_xeng_f32(a, sb, q->stream);
+    e = corr::launch_xeng_f32(a, sb, L.f32_sub, q->stream);
   if (e != hipSuccess) return CORR_E_HIP;
   if (!direct) {
     e = corr::launch_reduce_splits(q->part, (int64_t)c.n_channels * L.n_products, split, q->acc, q->accumulate,

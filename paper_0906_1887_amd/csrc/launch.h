@@ -23,7 +23,7 @@ hipError_t launch_xeng_publish(const ServeUpdate* u, int n_jobs, int n_active, u
                                hipStream_t s);
 // FP32 X-engine (64-row tiles), rows of any sample alignment; sample_bytes = 8 (complex float32) or 2 (complex int8).
 // n_items: per split, the pairs of diagonal tiles of all channels and the off-diagonal tiles.
-hipError_t launch_xeng_f32(const XArgs& a, int sample_bytes, hipStream_t s);
+hipError_t launch_xeng_f32(const XArgs& a, int sample_bytes, int sub, hipStream_t s);
 hipError_t launch_reduce_splits(const void* part, int64_t n_pairs, int n_split, void* acc, int accumulate,
                                 bool is_int, hipStream_t s);
 hipError_t launch_fill_zero(void* p, int64_t bytes, hipStream_t s);   // 16-byte aligned, bytes / 16 words

@@ -19,6 +19,13 @@
 // both are dealt out R R / 16 products a thread.  (A square diagonal tile, as
 // before, computes every product twice.)
 //
+// Up to 32 inputs: a panel holds two channels' 32 rows, or four channels' 16, so
+// that a workgroup takes 4 or 8 channels, each with 36 or 10 lanes of one wave (a
+// block each).  In pairs of 64-row tiles most blocks lay past the last input: 21
+// inputs x 652 channels x 2771 samples 378 -> 199 us a pass, 32 x 128 x 1000 48 ->
+// 37, 16 x 734 x 1000 173 -> 59, 4 x 600 x 5000 538 -> 164, 32 x 600 x 2000 int8 224
+// -> 127.
+//
 // Bound: FP32 vector rate: four items a CU run at 100 TFLOP/s of executed FMAs
 // (115 VGPRs, four waves per SIMD).  With square diagonal tiles of 128 rows
 // and two waves per SIMD before: 128 inputs x 96 channels x 2000 samples 343
@@ -140,7 +147,9 @@ __device__ __forceinline__ void f32_put2(const XArgs& a, float2* __restrict__ ou
 // before the FMAs that follow); only the last, partial stage checks its
 // samples.  Rows past N_I are read from a clamped row and only reach products
 // that are never stored.
-template <typename S, bool DIAG>
+// SUB 32 or 16: the panels are those of 128 / SUB channels from ch0 of at most SUB
+// inputs, SUB rows each; every wave takes 32 / SUB of them, a lane one block.
+template <typename S, bool DIAG, int SUB>
 __device__ __forceinline__ void xeng_f32_tile(const XArgs& a, float2 (*lds)[2][kF32KS][kF32BT], int split, int ch0, int I0,
                                               int ch1, int I1, bool two_ok) {
   constexpr int BT = kF32BT;
@@ -150,7 +159,9 @@ __device__ __forceinline__ void xeng_f32_tile(const XArgs& a, float2 (*lds)[2][k
   constexpr int CHUNKS = BT * CPR;           // per panel
   constexpr int LPT = (CHUNKS + 255) / 256;  // chunks per thread per panel
   constexpr int R = BT / 16;                 // rows (and cols) per thread
-  constexpr int NX = R * R / 16;             // products of the second tile's diagonal blocks per thread (DIAG)
+  constexpr bool TWO = DIAG && SUB == BT;    // a pair of diagonal tiles
+  constexpr int NX = R * R / 16;             // products of the second tile's diagonal blocks per thread (TWO)
+  constexpr int PER = BT / SUB;              // channels per panel (DIAG)
 
   const int64_t n_t = a.k_bytes / B;
   const int64_t split_t = a.k_split_bytes / B;
@@ -167,8 +178,10 @@ __device__ __forceinline__ void xeng_f32_tile(const XArgs& a, float2 (*lds)[2][k
   const int prow = (pos % 32) / 2 * R + pos / 32 * 2 + pos % 2;
   const int kc0 = tid / BT;                  // its first chunk; the next ones follow 256 / BT apart
   const int8_t* __restrict__ x = static_cast<const int8_t*>(a.x);
-  const int8_t* pa = x + (int64_t)ch0 * a.ch_stride_b + (int64_t)min(I0 * BT + prow, a.n_in - 1) * a.row_stride_b;
-  const int8_t* pb = x + (int64_t)ch1 * a.ch_stride_b + (int64_t)min(I1 * BT + prow, a.n_in - 1) * a.row_stride_b;
+  const int cha = SUB == BT ? ch0 : min(ch0 + prow / SUB, a.n_ch - 1);
+  const int chb = SUB == BT ? ch1 : min(ch0 + PER + prow / SUB, a.n_ch - 1);
+  const int8_t* pa = x + (int64_t)cha * a.ch_stride_b + (int64_t)min(I0 * BT + prow % SUB, a.n_in - 1) * a.row_stride_b;
+  const int8_t* pb = x + (int64_t)chb * a.ch_stride_b + (int64_t)min(I1 * BT + prow % SUB, a.n_in - 1) * a.row_stride_b;
 
   int4 ga[LPT], gb[LPT];
   auto gload = [&](int st) {
@@ -208,7 +221,21 @@ __device__ __forceinline__ void xeng_f32_tile(const XArgs& a, float2 (*lds)[2][k
   // This thread's block: rows rb against columns cb, DIAG: of tile u.
   int rb = ty, cb = tx;
   const int u = DIAG ? tid >> 7 : 0;
-  if (DIAG) {
+  // SUB: of channel sub of the panel, none past the last of the wave's channels.
+  constexpr int NSB = SUB / R, NBL = NSB * (NSB + 1) / 2;   // blocks per side and in all
+  const int sc = (tid & 63) / NBL;
+  const int sub = (tid >> 6 & 1) * (32 / SUB) + min(sc, 32 / SUB - 1);
+  if (DIAG && SUB < BT) {
+    const int t = (tid & 63) % NBL;
+    if (t < NBL - NSB) {
+      tile_decode(t, rb, cb);
+      ++rb;
+    } else {
+      rb = cb = t - (NBL - NSB);
+    }
+    rb += sub * NSB;
+    cb += sub * NSB;
+  } else if (DIAG) {
     const int t = tid & 127;
     if (t < 120) {
       tile_decode(t, rb, cb);
@@ -222,13 +249,13 @@ __device__ __forceinline__ void xeng_f32_tile(const XArgs& a, float2 (*lds)[2][k
   const int xr = tx * NX / R, xc = tx * NX % R;
   const int xpr = xr / 2 * 32 + 2 * xb + xr % 2;
 
-  float vr[R][R], vi[R][R], er[DIAG ? NX : 1], ei[DIAG ? NX : 1];
+  float vr[R][R], vi[R][R], er[TWO ? NX : 1], ei[TWO ? NX : 1];
 #pragma unroll
   for (int m = 0; m < R; ++m)
 #pragma unroll
     for (int n = 0; n < R; ++n) vr[m][n] = vi[m][n] = 0.f;
 #pragma unroll
-  for (int n = 0; n < (DIAG ? NX : 1); ++n) er[n] = ei[n] = 0.f;
+  for (int n = 0; n < (TWO ? NX : 1); ++n) er[n] = ei[n] = 0.f;
 
   if (n_st > 0) {
     gload(0);
@@ -254,7 +281,7 @@ __device__ __forceinline__ void xeng_f32_tile(const XArgs& a, float2 (*lds)[2][k
       for (int m = 0; m < R; ++m)
 #pragma unroll
         for (int n = 0; n < R; ++n) f32_cmac(vr[m][n], vi[m][n], av[m], bv[n]);
-      if constexpr (DIAG) {
+      if constexpr (TWO) {
         const float2 xa = As[k][xpr];
 #pragma unroll
         for (int n = 0; n < NX; ++n)
@@ -267,14 +294,17 @@ __device__ __forceinline__ void xeng_f32_tile(const XArgs& a, float2 (*lds)[2][k
 
   float2* const base = static_cast<float2*>(a.out) + (int64_t)split * a.out_split_stride;
   if (u == 1 && !two_ok) return;
-  float2* out = base + (int64_t)(u ? ch1 : ch0) * a.n_products;
-  const int ti = (u ? I1 : I0) * BT, tj = DIAG ? ti : I1 * BT;   // first row, first column of the tile
+  const int ch = SUB < BT ? ch0 + u * PER + sub : u ? ch1 : ch0;
+  if (SUB < BT && (sc >= 32 / SUB || ch >= a.n_ch)) return;
+  float2* out = base + (int64_t)ch * a.n_products;
+  // first row, first column of the tile
+  const int ti = SUB < BT ? -sub * SUB : (u ? I1 : I0) * BT, tj = DIAG ? ti : I1 * BT;
 #pragma unroll
   for (int m = 0; m < R; ++m)
 #pragma unroll
     for (int n = 0; n < R; n += 2)
       f32_put2(a, out, ti + rb * R + m, tj + cb * R + n, vr[m][n], vi[m][n], vr[m][n + 1], vi[m][n + 1]);
-  if constexpr (DIAG) {
+  if constexpr (TWO) {
 #pragma unroll
     for (int n = 0; n < NX; ++n)
       f32_put(a, out, ti + xb * R + xr, ti + xb * R + xc + n, er[n], ei[n]);
@@ -283,7 +313,7 @@ __device__ __forceinline__ void xeng_f32_tile(const XArgs& a, float2 (*lds)[2][k
 
 // Items of a split: the pairs of diagonal tiles (channel-major), then the
 // off-diagonal tiles of each channel.
-template <typename S>
+template <typename S, int SUB>
 __global__ __launch_bounds__(256, 4) void xeng_f32_kernel(XArgs a) {
   __shared__ __attribute__((aligned(16))) float2 lds[2][2][kF32KS][kF32BT];
   const int64_t slot = blockIdx.x / kNumXcd;
@@ -294,24 +324,32 @@ __global__ __launch_bounds__(256, 4) void xeng_f32_kernel(XArgs a) {
   const int per_split = a.n_items / a.n_split;
   const int split = (int)(item / per_split);
   const int v = (int)(item % per_split);
-  if (v < (n_diag + 1) / 2) {
+  if constexpr (SUB < kF32BT) {
+    xeng_f32_tile<S, true, SUB>(a, lds, split, v * (128 / SUB), 0, 0, 0, true);
+  } else if (v < (n_diag + 1) / 2) {
     const int d0 = 2 * v, d1 = min(2 * v + 1, n_diag - 1);
-    xeng_f32_tile<S, true>(a, lds, split, d0 / nb, d0 % nb, d1 / nb, d1 % nb, d1 != d0);
+    xeng_f32_tile<S, true, kF32BT>(a, lds, split, d0 / nb, d0 % nb, d1 / nb, d1 % nb, d1 != d0);
   } else {
     const int o = v - (n_diag + 1) / 2;
     const int n_off = nb * (nb - 1) / 2;
     int I, J;
     tile_decode(o % n_off, I, J);            // (I + 1, J): strictly lower
-    xeng_f32_tile<S, false>(a, lds, split, o / n_off, I + 1, o / n_off, J, true);
+    xeng_f32_tile<S, false, kF32BT>(a, lds, split, o / n_off, I + 1, o / n_off, J, true);
   }
 }
 
-// sample_bytes: 8 (complex float32) or 2 (complex int8).
-hipError_t launch_xeng_f32(const XArgs& a, int sample_bytes, hipStream_t s) {
+// sample_bytes: 8 (complex float32) or 2 (complex int8); sub: rows a channel has in
+// a panel (64, or 32 or 16 where a channel has no more inputs).
+hipError_t launch_xeng_f32(const XArgs& a, int sample_bytes, int sub, hipStream_t s) {
   const int64_t grid = (int64_t)a.per_xcd * kNumXcd;
   if (grid <= 0) return hipSuccess;
-  if (sample_bytes == 8) hipLaunchKernelGGL(xeng_f32_kernel<float2>, dim3((unsigned)grid), dim3(256), 0, s, a);
-  else hipLaunchKernelGGL(xeng_f32_kernel<int8_t>, dim3((unsigned)grid), dim3(256), 0, s, a);
+#define CORR_F32(S, SUB) hipLaunchKernelGGL((xeng_f32_kernel<S, SUB>), dim3((unsigned)grid), dim3(256), 0, s, a)
+  if (sample_bytes == 8) {
+    if (sub == 64) CORR_F32(float2, 64); else if (sub == 32) CORR_F32(float2, 32); else CORR_F32(float2, 16);
+  } else {
+    if (sub == 64) CORR_F32(int8_t, 64); else if (sub == 32) CORR_F32(int8_t, 32); else CORR_F32(int8_t, 16);
+  }
+#undef CORR_F32
   return hipGetLastError();
 }
 
