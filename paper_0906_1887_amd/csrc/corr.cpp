@@ -409,7 +409,23 @@ corr_status corr_internal_xengine(const corr_xpass* q) {
   a.n_tiles = L.n_tiles;
   a.n_split = split;
   if ((int64_t)c.n_channels * L.n_tiles * split > 0x7FFFFFFFll / 2) return CORR_E_INVAL;
-  const int64_t items = L.items * split;
+  // FP16 converting, 129 to 256 inputs: one workgroup per channel and split reads
+  // each row once (the splits, and so the sums, stay as they are).  It pays where its
+  // workgroups fill half of the rounds of 256 that they make and run long enough
+  // to cover their start: 256 inputs x 512 channels x 4096 samples 1276 -> 940 us, 300
+  // channels (59 %) x 2000 471 -> 420, 260 (51 %) 428 -> 400; with 125 samples each
+  // (40 x 1000) 80 -> 82, with 273 (200 x 33 x 3000) 95 -> 96, with 512 257 -> 246.
+  int bt = L.bt;
+  int64_t items = L.items * split;
+  if (q->elem == corr::kElemF16Cvt && c.n_inputs > 128 && c.n_inputs <= 256 &&
+      a.row_stride_b < (int64_t(1) << 24) && std::min(n_samples, sp.samples) >= 400) {
+    const int64_t wg = (int64_t)c.n_channels * split;
+    if (2 * wg >= (wg + 255) / 256 * 256) {
+      bt = 256;
+      items = wg;
+      a.n_tiles = 1;
+    }
+  }
   a.n_items = (int32_t)items;
   a.per_xcd = (int32_t)((items + corr::kNumXcd - 1) / corr::kNumXcd);
   const bool direct = (split == 1);
@@ -425,7 +441,7 @@ corr_status corr_internal_xengine(const corr_xpass* q) {
   hipError_t e;
   const bool is_int = (c.engine == CORR_X_I8);
   if (q->elem >= 0)
-    e = corr::launch_xeng_mfma(a, q->elem, L.bt, q->stream);  // staged FP16 / FP8 rows and CI4 rows are aligned
+    e = corr::launch_xeng_mfma(a, q->elem, bt, q->stream);  // staged FP16 / FP8 rows and CI4 rows are aligned
   else if (c.engine == CORR_X_I8)
     e = aligned ? corr::launch_xeng_mfma(a, corr::kElemI8, L.bt, q->stream)
                 : corr::launch_xeng_i8u(a, L.bt, q->stream);

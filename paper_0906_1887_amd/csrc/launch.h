@@ -12,7 +12,8 @@ struct FArgs;
 // int8 MFMA X-engine for rows of any (2-byte) alignment; bt = 64 or 128.
 hipError_t launch_xeng_i8u(const XArgs& a, int bt, hipStream_t s);
 // Matrix-core X-engine for 16-byte aligned rows; elem = kElemI8 / kElemCI4 /
-// kElemF16 / kElemF8 / kElemF16Cvt / kElemF8Cvt (bt 64 or 128) or kElemF32 (bt 64).
+// kElemF16 / kElemF8 / kElemF16Cvt / kElemF8Cvt (bt 64 or 128; kElemF16Cvt also 256: one
+// workgroup per channel) or kElemF32 (bt 64).
 hipError_t launch_xeng_mfma(const XArgs& a, int elem, int bt, hipStream_t s);
 // Serving grid over the device job queue (int8, aligned rows, 128-row tiles);
 // grid = workgroups.

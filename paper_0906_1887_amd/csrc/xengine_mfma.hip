@@ -1247,6 +1247,187 @@ __global__ __launch_bounds__(256, 2) void xeng_mfma_128_kernel(XArgs a) {
   }
 }
 
+// The converting FP16 engine on 129 to 256 inputs, one workgroup per channel: 8 waves
+// cover the 36 blocks of 32 x 32 on or below the diagonal, so that every float32
+// row is read once, where three 128-row tiles read each twice and find the second
+// reading in L2 only while they keep step (4.9 GB read for 4.3 of samples at 256
+// x 512 x 4096; 8.1 with loads that do not wait for each other).  256 x 512 x 4096
+// with its read-out 1276 -> 940 us, 130 x 512 x 2000 554 -> 374, 200 x 256 x 2000 346 ->
+// 264.  Bound by the loads of float32 samples (5 TB/s).
+//
+// Block rows come in pairs (7 - p, p) of 9 blocks; waves p and p + 4 (one SIMD)
+// take 5 and 4 of them: 160 accumulators, and two stages of samples in flight (4
+// float4 per thread and stage).  A wave reads both operands of every block from
+// LDS; a wave of 4 repeats its last one, because a branch around a block made the
+// compiler spill 215 registers.  Samples past
+// the pass are zero; rows past N_I are read from a clamped row and never stored.
+__device__ __forceinline__ void mfma_tri_cvt(const XArgs& a, int8_t* lds, int ch, int split) {
+  constexpr int BT = 256, NT = 512;
+  constexpr int STAGE = BT * kMKC;
+  constexpr int SPS = kMKC / 4, NF = SPS / 2;     // samples, float4 per row and stage
+  constexpr int L = BT * NF / NT;                 // float4 per thread and stage
+  constexpr int PF = 2;                           // stages in flight in registers
+  constexpr int NB = 5;                           // blocks per wave, at most
+
+  const float* __restrict__ xc = reinterpret_cast<const float*>(static_cast<const int8_t*>(a.x) + (int64_t)ch * a.ch_stride_b);
+  const int64_t k0 = (int64_t)split * a.k_split_bytes;
+  const int64_t k1 = min(a.k_bytes, k0 + a.k_split_bytes);
+  const int n_st = k1 > k0 ? (int)((k1 - k0 + kMKC - 1) / kMKC) : 0;
+  const int64_t t0 = k0 / 4, t1 = k1 / 4;          // sample range of the pass
+  const int n_full = (int)((t1 - t0) / SPS);       // stages whose samples are all there
+  const int64_t rsf = a.row_stride_b / 4;
+
+  const int tid = threadIdx.x;
+  const int lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+
+  // This thread's loads: float4 f of rows tid / NF + 64 q.
+  const int f = tid % NF;
+  uint32_t src[L];   // 32 bits suffice: the caller has checked the stride
+#pragma unroll
+  for (int q = 0; q < L; ++q) src[q] = (uint32_t)min(tid / NF + NT / NF * q, a.n_in - 1) * (uint32_t)rsf + 4 * f;
+  // (64 rows on, the swizzle is the same)
+  const int q_lds = (tid / NF) * kMKC + 16 * ((f >> 1) ^ swz(tid / NF)) + 8 * (f & 1);
+  float4 R[PF][L];
+  auto gload_full = [&](auto S, int st) {   // st < n_full
+    constexpr int sl = decltype(S)::value;
+    const float* base = xc + (t0 + (int64_t)st * SPS) * 2;
+#pragma unroll
+    for (int q = 0; q < L; ++q) R[sl][q] = load16_any<float4>(base + src[q]);
+  };
+  auto gload = [&](auto S, int st) {
+    constexpr int sl = decltype(S)::value;
+    const int64_t t = t0 + (int64_t)st * SPS + 2 * f;
+#pragma unroll
+    for (int q = 0; q < L; ++q) {
+      const float* g = xc + (t0 + (int64_t)st * SPS) * 2 + src[q];
+      float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
+      if (t + 2 <= t1) {
+        v = load16_any<float4>(g);
+      } else if (t < t1) {
+        v.x = g[0];
+        v.y = g[1];
+      }
+      R[sl][q] = v;
+    }
+  };
+  auto cvt_store = [&](auto S, int buf) {
+    constexpr int sl = decltype(S)::value;
+#pragma unroll
+    for (int q = 0; q < L; ++q) {
+      const float4 v = R[sl][q];
+      *reinterpret_cast<uint2*>(lds + buf * STAGE + q_lds + NT / NF * kMKC * q) = make_uint2(pack_f16x2(v.x, v.y), pack_f16x2(v.z, v.w));
+    }
+  };
+
+  // This wave's blocks (not stored where they are a repetition or past the last input).
+  const int p = wave & 3, q0 = wave < 4 ? 0 : 5;
+  int br[NB], bc[NB];
+  bool on[NB];
+#pragma unroll
+  for (int k = 0; k < NB; ++k) {
+    const int q = min(q0 + k, 8);
+    br[k] = q < 8 - p ? 7 - p : p;
+    bc[k] = q < 8 - p ? q : q - (8 - p);
+    on[k] = q0 + k <= 8 && br[k] * 32 < a.n_in;
+  }
+  v16f vr[NB], vi[NB];
+#pragma unroll
+  for (int k = 0; k < NB; ++k)
+#pragma unroll
+    for (int r = 0; r < 16; ++r) vr[k][r] = vi[k][r] = 0.f;
+
+  const int frow = lane & 31, g = lane >> 5;
+  const int fr[2] = {frow * kMKC + 16 * (g ^ swz(frow)), frow * kMKC + 16 * ((2 + g) ^ swz(frow))};
+  auto compute = [&](int buf) {
+    const int8_t* S = lds + buf * STAGE;
+#pragma unroll
+    for (int k = 0; k < NB; ++k) {
+      v4i af[2], bf[2];
+#pragma unroll
+      for (int h = 0; h < 2; ++h) {
+        af[h] = *reinterpret_cast<const v4i*>(S + br[k] * 32 * kMKC + fr[h]);
+        bf[h] = *reinterpret_cast<const v4i*>(S + bc[k] * 32 * kMKC + fr[h]);
+      }
+#pragma unroll
+      for (int h = 0; h < 2; ++h) mfma16<kElemF16>(af[h], bf[h], vr[k]);
+#pragma unroll
+      for (int h = 0; h < 2; ++h) mfma16<kElemF16>(rotm4<kElemF16>(af[h]), bf[h], vi[k]);
+      __builtin_amdgcn_sched_barrier(0);
+    }
+  };
+  // This wave's LDS accesses are done, then every wave's (loads stay in flight).
+  auto barrier = [&] { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); };
+
+  using S0 = std::integral_constant<int, 0>;
+  using S1 = std::integral_constant<int, 1>;
+  const bool deep = n_full > PF + 1;
+  if (deep) {
+    gload_full(S0{}, 0);
+    gload_full(S1{}, 1);
+    cvt_store(S0{}, 0);
+    gload_full(S0{}, 2);
+  } else {
+    if (0 < n_st) gload(S0{}, 0);
+    if (1 < n_st) gload(S1{}, 1);
+    if (0 < n_st) cvt_store(S0{}, 0);
+    if (2 < n_st) gload(S0{}, 2);
+  }
+  barrier();
+  // Stage st lives in register slot st % PF; iteration st converts stage st + 1
+  // (freeing its slot), refills that slot with stage st + 1 + PF and multiplies
+  // stage st.  FULL: these exist and are whole, so that no condition stands around
+  // the loads and the compiler waits for the oldest stage only.
+  auto step = [&](auto full, auto NX, int st) {
+    constexpr bool FULL = decltype(full)::value;
+    if (FULL || st + 1 < n_st) {
+      cvt_store(NX, (st + 1) & 1);
+      if constexpr (FULL) gload_full(NX, st + 1 + PF);
+      else if (st + 1 + PF < n_st) gload(NX, st + 1 + PF);
+    }
+    compute(st & 1);
+    barrier();
+  };
+  int st = 0;
+  if (deep)
+    for (; st + 2 + PF < n_full; st += 2) {
+      step(std::true_type{}, S1{}, st);
+      step(std::true_type{}, S0{}, st + 1);
+    }
+  for (; st < n_st; st += 2) {
+    step(std::false_type{}, S1{}, st);
+    if (st + 1 < n_st) step(std::false_type{}, S0{}, st + 1);
+  }
+
+  // Epilogue (32 x 32 accumulator layout: register r of lane l holds row
+  // 8*(r/4) + 4*(l/32) + r%4, column l%32).
+  float2* const out = static_cast<float2*>(a.out) + (int64_t)split * a.out_split_stride + (int64_t)ch * a.n_products;
+#pragma unroll
+  for (int k = 0; k < NB; ++k) {
+    const int j = bc[k] * 32 + (lane & 31);
+#pragma unroll
+    for (int h = 0; h < 16; h += 8) {
+      uint32_t off[8];
+      float2 v[8];
+#pragma unroll
+      for (int r = h; r < h + 8; ++r) {
+        const int i = br[k] * 32 + 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3);
+        off[r - h] = on[k] && i < a.n_in && j <= i ? (uint32_t)tri_index(i, j) : kNoProduct;
+        v[r - h] = make_float2(vr[k][r], i == j ? 0.f : vi[k][r]);
+      }
+      put_products(out, off, v, a.accumulate);
+    }
+  }
+}
+
+__global__ __launch_bounds__(512, 1) void xeng_cvt_tri_kernel(XArgs a) {
+  __shared__ __attribute__((aligned(1024))) int8_t lds[2 * 256 * kMKC];
+  const int64_t slot = blockIdx.x / kNumXcd;
+  const int64_t item = xcd_item(blockIdx.x, a.per_xcd);
+  if (slot >= a.per_xcd || item >= a.n_items) return;
+  mfma_tri_cvt(a, lds, (int)(item / a.n_split), (int)(item % a.n_split));
+}
+
 // Waves per workgroup of the converting engines (one workgroup per CU).  FP16:
 // 8 (two per SIMD, 64 x 32 wave parts, 177 VGPRs), 8 % faster on C4 than 4
 // waves of 64 x 64.  FP8 stages twice the samples per row and would spill
@@ -1706,6 +1887,8 @@ hipError_t launch_xeng_mfma(const XArgs& a, int elem, int bt, hipStream_t s) {
     hipLaunchKernelGGL((xeng_cvt_64_kernel<kElemF16Cvt>), g, b, 0, s, a);
   } else if (elem == kElemF8Cvt && bt == 64) {
     hipLaunchKernelGGL((xeng_cvt_64_kernel<kElemF8Cvt>), g, b, 0, s, a);
+  } else if (elem == kElemF16Cvt && bt == 256) {
+    hipLaunchKernelGGL(xeng_cvt_tri_kernel, g, dim3(512), 0, s, a);
   } else if (elem == kElemF16Cvt) {
     hipLaunchKernelGGL((xeng_cvt_128_kernel<kElemF16Cvt>), g, dim3(cvt_waves<kElemF16Cvt>() * 64), 0, s, a);
   } else if (elem == kElemF8Cvt) {
