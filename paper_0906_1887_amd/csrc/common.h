@@ -134,43 +134,4 @@ __device__ __forceinline__ float e4m3_scale(float m) {
   return s;
 }
 
-// Serving queue (xeng_serve_kernel).  The host publishes each admitted job in
-// a slot under a generation of its own; the slot's claim word holds that
-// generation in its upper half and counts claimed items in its lower one, so
-// that one fetch-and-add both claims an item and says whose it is.  Every job
-// runs 128-row tiles.
-constexpr int kServeLine = 32;             // uint32 per 128-byte line
-constexpr int kServeSlots = 64;
-struct ServeJob {
-  XArgs x;                  // the job's pass: samples, strides, output, n_tiles, n_items (channel x tile)
-  uint32_t* flag;           // completion word in host memory (device view)
-  uint32_t flag_value;      // written there when the job's last item is done
-  uint32_t gen;             // the job's generation in its slot
-};
-// One entry of the list of active slots: 2 words, slot and n_items (upper
-// half), then generation.
-constexpr uint64_t serve_entry(int slot, int32_t n_items) { return (uint64_t)(uint32_t)slot | (uint64_t)(uint32_t)n_items << 32; }
-// One update of the queue (xeng_publish_kernel), in mapped host memory: the
-// admitted jobs with their slots, and the new list of active slots.
-struct ServeUpdate {
-  uint64_t active[2 * kServeSlots];
-  int32_t slot[kServeSlots];
-  ServeJob job[kServeSlots];
-};
-struct ServeQueue {
-  ServeJob* slots;          // [n_slots]
-  uint64_t* claim;          // slot s at claim[s * kServeLine / 2]
-  uint32_t* done;           // slot s at done[s * kServeLine]: items done of its job
-  uint64_t* active;         // [1 + 2 n_slots]: count and version (upper half) of the list, then its entries
-  uint64_t* last_claim;     // wall clock (s_memrealtime ticks) of the latest claim or grid start
-  uint32_t* closing;        // highest grid generation that has closed (no more claims)
-  uint32_t* host_closing;   // the same, in host memory (device view) for the scheduler
-  uint64_t* host_claimed;   // host memory (device view): slot s at [s * kServeLine / 2 + 1] receives
-                            // the job's generation once its last item is claimed
-  uint32_t gen;             // this launch's generation (increasing from 1)
-  uint32_t idle_ticks;      // queue idle this long (100 MHz ticks): the grid closes
-  int32_t n_slots;
-  int32_t max_polls;        // bound on one workgroup's empty polls (a safety net)
-};
-
 }  // namespace corr

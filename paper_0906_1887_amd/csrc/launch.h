@@ -4,6 +4,7 @@
 #include <hip/hip_runtime.h>
 
 #include "common.h"
+#include "serve_queue.h"
 
 namespace corr {
 

@@ -91,6 +91,7 @@ struct Job {
   corr::ServeJob sj{};                 // its pass, as published
   bool claimed_all = false;            // the device has claimed every item
   uint32_t flag_value = 0;
+  uint32_t gen = 0;                    // its generation in its slot
   corr_plan* plan = nullptr;
   int stream = -1;
   int64_t n_out = 0;
@@ -176,7 +177,7 @@ QueueLayout queue_layout() {
   q.done = off;
   off = align_up(off + kSlots * corr::kServeLine * 4);
   q.active = off;
-  off = align_up(off + (2 * kSlots + 1) * 8);
+  off = align_up(off + (kSlots + 1) * 8);
   q.last_claim = off;
   off = align_up(off + 128);
   q.closing = off;
@@ -271,9 +272,7 @@ hipError_t publish(corr_sched* s) {
   for (int q = 0; q < kSlots; ++q) {
     const Job* j = s->slot_job[q];
     if (j && j->state.load() == kRunning && !j->claimed_all) {
-      u.active[2 * n] = corr::serve_entry(q, j->sj.x.n_items);
-      u.active[2 * n + 1] = j->sj.gen;
-      ++n;
+      u.active[n++] = corr::serve_entry(q, j->gen);
     }
   }
   const hipError_t r = corr::launch_xeng_publish(
@@ -343,7 +342,8 @@ void launch_queued(corr_sched* s, Job* j) {
   if (j->flag_value == 0) j->flag_value = ++s->next_flag;
   sj.flag = s->d_flags + (size_t)j->slot * corr::kServeLine;
   sj.flag_value = j->flag_value;
-  sj.gen = ++s->slot_gen[j->slot];
+  j->gen = ++s->slot_gen[j->slot];
+  sj.ident = corr::serve_ident(j->gen, a.n_items);
   s->batch.push_back(j);
 }
 
@@ -434,7 +434,7 @@ void collect_queue(corr_sched* s) {
       const uint64_t c = __atomic_load_n(reinterpret_cast<const uint64_t*>(s->flags) +
                                              (size_t)j->slot * (corr::kServeLine / 2) + 1,
                                          __ATOMIC_ACQUIRE);
-      if (c == j->sj.gen) {
+      if (c == j->gen) {
         // every item is claimed: the next update lists the job no more (until
         // then each workgroup looks at it once and remembers)
         j->claimed_all = true;

@@ -1667,10 +1667,8 @@ __global__ __launch_bounds__(256, 2) void xeng_mfma_kernel(XArgs a) {
 // channels and 16 to 128 inputs took 940 us as a batch
 // (with one update launch for three copies a job), 700 with the add, and 460
 // once a tile's products went through to memory instead of a release fence per
-// tile (1500 at first).  A
-// workgroup whose list entry is out of date may claim an item of the slot's
-// next job: the word's generation tells, and the job record is that job's (it
-// is written before the word, and not replaced while an item is unfinished).
+// tile (1500 at first).  serve_claim (serve_queue.h) says why a claim made
+// from an entry of an old list is sound.
 //
 // A grid ends as a whole: once no workgroup has claimed an item for
 // idle_ticks of the 100 MHz wall clock, the first workgroup to notice closes
@@ -1683,81 +1681,55 @@ __device__ __forceinline__ uint64_t sys_load64(const void* p) {
   return __hip_atomic_load(static_cast<const uint64_t*>(p), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
 }
 
-// What a workgroup remembers of the list between claims.
-struct ServeView {
-  uint32_t turn;      // its place in the round robin
-  uint32_t n;         // length and version of the list when it last looked
-  uint32_t version;
-  uint64_t spent;     // places of that list whose jobs have no unclaimed item
-  bool fresh;         // this list's jobs' samples are visible (acquired since it was seen)
-};
-
-// One lane: claim one item; the slot, or -1 when the grid has closed (or this
-// workgroup has polled max_polls times without work).  *word receives the
-// claim word.  Memory takes microseconds to answer while the grid streams
-// samples, so the next entry is fetched together with the list's length, on
-// the guess that the list is the one last seen.
-__device__ int serve_claim(const ServeQueue& q, ServeView& v, uint64_t* word) {
-  for (int poll = 0; poll < q.max_polls; ++poll) {
-    uint32_t at = v.turn % v.n;
-    const uint32_t closing = __hip_atomic_load(q.closing, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    const uint64_t head = sys_load64(q.active);
-    uint64_t e0 = sys_load64(q.active + 1 + 2 * at), e1 = sys_load64(q.active + 2 + 2 * at);
-    if (closing >= q.gen) return -1;
-    const uint32_t n = min((uint32_t)head, (uint32_t)q.n_slots);
-    bool fetched = n == v.n;
-    if ((uint32_t)(head >> 32) != v.version || !fetched) {
-      v.version = (uint32_t)(head >> 32);
-      v.spent = 0;
-      v.fresh = false;
-      if (n > 0) v.n = n;
-    }
-    for (uint32_t a = 0; a < n; ++a, fetched = false) {
-      at = v.turn++ % n;
-      if ((v.spent >> at) & 1u) continue;
-      if (!fetched) {
-        e0 = sys_load64(q.active + 1 + 2 * at);
-        e1 = sys_load64(q.active + 2 + 2 * at);
-      }
-      const uint32_t s = (uint32_t)e0;
-      if (s >= (uint32_t)q.n_slots) continue;
-      const uint64_t w = __hip_atomic_fetch_add(q.claim + (size_t)s * (kServeLine / 2), 1ull, __ATOMIC_RELAXED,
-                                                __HIP_MEMORY_SCOPE_AGENT);
-      // Claimed, unless the count is past the items of the generation's job.
-      uint32_t limit = (uint32_t)(e0 >> 32);
-      if ((uint32_t)(w >> 32) != (uint32_t)e1) {
-        const ServeJob* j = q.slots + s;
-        const uint64_t id = sys_load64(&j->flag_value);   // flag_value, gen
-        v.fresh = false;   // a job published after the list was seen
-        limit = (uint32_t)(id >> 32) == (uint32_t)(w >> 32)
-                    ? (uint32_t)__hip_atomic_load(&j->x.n_items, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM)
-                    : 0u;
-      }
-      if ((uint32_t)w >= limit) {
-        v.spent |= 1ull << at;
-        continue;
-      }
-      __hip_atomic_fetch_max(q.last_claim, (uint64_t)wall_clock64(), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      // the job's last item: tell the host, which then lists the job no more
-      if ((uint32_t)w + 1 == limit)
-        __hip_atomic_store(q.host_claimed + (size_t)s * (kServeLine / 2) + 1, w >> 32, __ATOMIC_RELAXED,
-                           __HIP_MEMORY_SCOPE_SYSTEM);
-      *word = w;
-      return (int)s;
-    }
+// The queue's memory as the kernels reach it: loads and stores of system scope
+// go past the caches, and every value is there before what depends on it is
+// issued.
+struct ServeMemory {
+  __device__ uint64_t load(const uint64_t* p) { return sys_load64(p); }
+  __device__ uint32_t load_agent(const uint32_t* p) {
+    return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  }
+  // two loads in flight together
+  __device__ void load2(const uint64_t* p0, const uint64_t* p1, uint64_t& v0, uint64_t& v1) {
+    v0 = load(p0);
+    v1 = load(p1);
+  }
+  // *claim += 1 (w: its former value) and a load, in flight together
+  __device__ void add_load(uint64_t* claim, const uint64_t* p, uint64_t& w, uint64_t& v) {
+    w = __hip_atomic_fetch_add(claim, 1ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    v = load(p);
+  }
+  __device__ void store(uint64_t* p, uint64_t v) {
+    __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+  }
+  template <typename T>
+  __device__ void exchange(T* p, T v) {
+    __hip_atomic_exchange(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  }
+  __device__ void settle() {
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    __syncthreads();
+  }
+  // An item was claimed: the grid is busy.
+  __device__ void claimed(const ServeQueue& q) {
+    __hip_atomic_fetch_max(q.last_claim, (uint64_t)wall_clock64(), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  }
+  // Nothing to claim: true once the grid has closed, which the first workgroup
+  // to see the queue idle for idle_ticks does; else wait a little.
+  __device__ bool idle(const ServeQueue& q) {
     const uint64_t last = __hip_atomic_load(q.last_claim, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     if ((uint64_t)wall_clock64() > last + q.idle_ticks) {
-      uint32_t c = __hip_atomic_load(q.closing, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      uint32_t c = load_agent(q.closing);
       while (c < q.gen && !__hip_atomic_compare_exchange_strong(q.closing, &c, q.gen, __ATOMIC_RELAXED,
                                                                   __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) {
       }
       if (c < q.gen) __hip_atomic_store(q.host_closing, q.gen, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
-      return -1;
+      return true;
     }
     __builtin_amdgcn_s_sleep(8);
+    return false;
   }
-  return -1;
-}
+};
 
 // The job's arguments and the claimed item pass through the start of the
 // tile's LDS buffer (one LDS object per kernel: a second one makes the
@@ -1775,13 +1747,14 @@ __global__ __launch_bounds__(256, 2) void xeng_serve_kernel(ServeQueue q) {
   ServeClaim* sc = reinterpret_cast<ServeClaim*>(lds);
   if (threadIdx.x == 0)   // a new grid counts as activity: it lingers idle_ticks before it may close
     __hip_atomic_fetch_max(q.last_claim, (uint64_t)wall_clock64(), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  ServeMemory mem;
   ServeView view{blockIdx.x, 1, 0, 0, false};
   for (;;) {
     __syncthreads();   // the previous tile's LDS reads are done
     if (threadIdx.x < 64) {
       int slot = -1;
       uint64_t word = 0;
-      if (threadIdx.x == 0) slot = serve_claim(q, view, &word);
+      if (threadIdx.x == 0) slot = serve_claim(mem, q, view, &word);
       slot = __builtin_amdgcn_readfirstlane(slot);
       // Samples may have been written since the grid started, into memory that
       // this CU or XCD has cached: drop what it holds, once for each list seen.
@@ -1830,38 +1803,16 @@ __global__ __launch_bounds__(256, 2) void xeng_serve_kernel(ServeQueue q) {
   }
 }
 
-// Publish a batch of admitted jobs to the queue of a running serving grid: the
-// jobs' records and done counts, then their slots' claim words (no item of a
-// job is claimed before its claim word is set, so its record is seen first),
-// then the list of active slots.  The slots' former jobs are complete.  Every
-// store goes through to memory (system scope, or an atomic) and is
-// acknowledged before the next step, so no fence has to write back an L2.  One
-// launch a batch: as three copies a job the queue updates took 8 us each on
-// the device and 25 us a job on the host.
+// Publish a batch of admitted jobs to the queue of a running serving grid
+// (serve_publish).  Every store goes through to memory (system scope, or an
+// atomic) and is acknowledged before the next step, so no fence has to write
+// back an L2.  One launch a batch: as three copies a job the queue updates took
+// 8 us each on the device and 25 us a job on the host.
 __global__ __launch_bounds__(256) void xeng_publish_kernel(const ServeUpdate* __restrict__ u, int n_jobs, int n_active,
                                                            uint32_t version, ServeQueue q) {
-  constexpr int kWords = sizeof(ServeJob) / 8;
-  const uint64_t* src = reinterpret_cast<const uint64_t*>(u->job);
-  for (int k = threadIdx.x; k < n_jobs * kWords; k += 256) {
-    uint64_t* dst = reinterpret_cast<uint64_t*>(q.slots + u->slot[k / kWords]) + k % kWords;
-    __hip_atomic_store(dst, src[k], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
-  }
-  const int slot = threadIdx.x < n_jobs ? u->slot[threadIdx.x] : 0;
-  const uint64_t word = threadIdx.x < n_jobs ? (uint64_t)u->job[threadIdx.x].gen << 32 : 0;
-  const uint64_t entry = threadIdx.x < 2 * n_active ? u->active[threadIdx.x] : 0;
-  if (threadIdx.x < n_jobs)
-    __hip_atomic_exchange(q.done + (size_t)slot * kServeLine, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-  __syncthreads();
-  if (threadIdx.x < n_jobs)
-    __hip_atomic_exchange(q.claim + (size_t)slot * (kServeLine / 2), word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-  __syncthreads();
-  if (threadIdx.x < 2 * n_active)
-    __hip_atomic_store(q.active + 1 + threadIdx.x, entry, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
-  if (threadIdx.x == 255)
-    __hip_atomic_store(q.active, (uint64_t)version << 32 | (uint64_t)n_active, __ATOMIC_RELAXED,
-                       __HIP_MEMORY_SCOPE_SYSTEM);
+  static_assert(kServeSlots < 256, "a thread per slot, and one for the list's head");
+  ServeMemory mem;
+  serve_publish(mem, u, n_jobs, n_active, version, q, (int)threadIdx.x, 256);
 }
 
 hipError_t launch_xeng_publish(const ServeUpdate* u, int n_jobs, int n_active, uint32_t version, const ServeQueue& q,
