@@ -11,8 +11,8 @@
 // Device queue (the batched path).  An admitted job is published in a slot
 // of a job queue in the arena's head: its pass (sample and result pointers,
 // shape) and its number of work items, one per (channel, 128-row baseline
-// tile), under a new generation of the slot; the jobs admitted together are
-// published by one small kernel.  A persistent serving grid (xeng_serve_kernel, as many
+// tile); the jobs admitted together are published by one small kernel, under
+// the number of that update.  A persistent serving grid (xeng_serve_kernel, as many
 // workgroups as the GPU holds at once but kCopyReserve) runs while published
 // work remains.  Its workgroups claim items round robin over the listed jobs,
 // so jobs that arrive while others run are taken up by the grid already on
@@ -91,7 +91,7 @@ struct Job {
   corr::ServeJob sj{};                 // its pass, as published
   bool claimed_all = false;            // the device has claimed every item
   uint32_t flag_value = 0;
-  uint32_t gen = 0;                    // its generation in its slot
+  uint32_t gen = 0;                    // the update that published it
   corr_plan* plan = nullptr;
   int stream = -1;
   int64_t n_out = 0;
@@ -216,10 +216,9 @@ struct corr_sched {
   hipEvent_t stage_ev[kStage] = {};
   bool stage_used[kStage] = {};
   int stage_next = 0;
-  uint32_t slot_gen[kSlots] = {};          // generation of each slot's latest job
   Job* slot_job[kSlots] = {};
   std::vector<int> free_slots;
-  uint32_t list_version = 0;               // of the list of active slots
+  uint32_t list_version = 0;               // number of the latest queue update
   uint32_t next_flag = 0;
   std::mutex mu;
   std::condition_variable cv;
@@ -264,20 +263,24 @@ hipError_t publish(corr_sched* s) {
   s->stage_used[k] = true;
   static_assert(sizeof(corr::ServeUpdate) <= kStageBytes, "an update fits its staging entry");
   corr::ServeUpdate& u = *reinterpret_cast<corr::ServeUpdate*>(s->stage + (size_t)k * kStageBytes);
+  if (++s->list_version == 0) ++s->list_version;   // 0: nothing published yet
   for (size_t b = 0; b < s->batch.size(); ++b) {
-    u.slot[b] = s->batch[b]->slot;
-    u.job[b] = s->batch[b]->sj;
+    Job* j = s->batch[b];
+    j->gen = s->list_version;
+    j->sj.ident = corr::serve_ident(j->gen, j->sj.x.n_items);
+    u.slot[b] = j->slot;
+    u.job[b] = j->sj;
   }
   int n = 0;
   for (int q = 0; q < kSlots; ++q) {
     const Job* j = s->slot_job[q];
     if (j && j->state.load() == kRunning && !j->claimed_all) {
-      u.active[n++] = corr::serve_entry(q, j->gen);
+      u.active[n++] = (uint64_t)q;
     }
   }
   const hipError_t r = corr::launch_xeng_publish(
       reinterpret_cast<const corr::ServeUpdate*>(s->d_stage + (size_t)k * kStageBytes), (int)s->batch.size(), n,
-      ++s->list_version, s->q, s->s_ctl);   // one slot a job, so at most kSlots
+      s->list_version, s->q, s->s_ctl);   // one slot a job, so at most kSlots
   if (r != hipSuccess) {
     s->stage_used[k] = false;
     return r;
@@ -342,8 +345,6 @@ void launch_queued(corr_sched* s, Job* j) {
   if (j->flag_value == 0) j->flag_value = ++s->next_flag;
   sj.flag = s->d_flags + (size_t)j->slot * corr::kServeLine;
   sj.flag_value = j->flag_value;
-  j->gen = ++s->slot_gen[j->slot];
-  sj.ident = corr::serve_ident(j->gen, a.n_items);
   s->batch.push_back(j);
 }
 

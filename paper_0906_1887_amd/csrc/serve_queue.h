@@ -9,10 +9,12 @@
 
 namespace corr {
 
-// The host publishes each admitted job in a slot under a generation of its
-// own; the slot's claim word holds that generation in its upper half and
-// counts claimed items in its lower one, so that one fetch-and-add both claims
-// an item and says whose it is.  Every job runs 128-row tiles.
+// The host publishes each admitted job in a slot.  The job's generation is the
+// number of the update that publishes it, so it differs from those of the
+// slot's other jobs and tells which of two jobs came later.  The slot's claim
+// word holds it in its upper half and counts claimed items in its lower one, so
+// that one fetch-and-add both claims an item and says whose it is.  Every job
+// runs 128-row tiles.
 constexpr int kServeLine = 32;             // uint32 per 128-byte line
 constexpr int kServeSlots = 64;
 struct ServeJob {
@@ -23,11 +25,9 @@ struct ServeJob {
   uint64_t ident;           // serve_ident: whose record this is and how many items it has, read as one word
 };
 constexpr uint64_t serve_ident(uint32_t gen, int32_t n_items) { return (uint64_t)gen << 32 | (uint32_t)n_items; }
-// One entry of the list of active slots: one word, so that it is never half of
-// one job's and half of another's.
-constexpr uint64_t serve_entry(int slot, uint32_t gen) { return (uint64_t)gen << 32 | (uint32_t)slot; }
 // One update of the queue (xeng_publish_kernel), in mapped host memory: the
-// admitted jobs with their slots, and the new list of active slots.
+// admitted jobs with their slots, and the new list of active slots (an
+// entry is a slot; whose job it holds, the claim tells).
 struct ServeUpdate {
   uint64_t active[kServeSlots];
   int32_t slot[kServeSlots];
@@ -55,7 +55,9 @@ struct ServeView {
   uint32_t n;         // length and version of the list when it last looked
   uint32_t version;
   uint64_t spent;     // places of that list whose jobs have no unclaimed item
-  bool fresh;         // this list's jobs' samples are visible (acquired since it was seen)
+  uint32_t acquired;  // the samples of jobs up to this update are visible to its loads
+  bool cold;          // nothing acquired yet
+  bool acquire;       // out: drop what the caches hold before the claimed job's samples are read
 };
 
 // One lane: claim one item; the slot, or -1 when the grid has closed (or this
@@ -74,6 +76,14 @@ struct ServeView {
 // that is not there.  (With the item count in the list, beside a generation in
 // a word of its own, an entry loaded while the slot's next job was listed could
 // give that job its predecessor's count.)
+//
+// Samples may have been written since the grid started, into memory that this
+// CU or XCD has cached.  What was published by an update was written before it,
+// so one acquire after the list's head or a claim word has shown update u makes
+// the samples of all jobs up to u visible, and a claim needs another one just
+// if its job is newer than that, whichever list led to it.  (Asking whether the
+// list had changed instead missed the job of a list whose entry was loaded
+// after the former list's head.)
 template <class M>
 __host__ __device__ inline int serve_claim(M& m, const ServeQueue& q, ServeView& v, uint64_t* word) {
   for (int poll = 0; poll < q.max_polls; ++poll) {
@@ -87,7 +97,6 @@ __host__ __device__ inline int serve_claim(M& m, const ServeQueue& q, ServeView&
     if ((uint32_t)(head >> 32) != v.version || !fetched) {
       v.version = (uint32_t)(head >> 32);
       v.spent = 0;
-      v.fresh = false;
       if (n > 0) v.n = n;
     }
     for (uint32_t a = 0; a < n; ++a, fetched = false) {
@@ -100,12 +109,15 @@ __host__ __device__ inline int serve_claim(M& m, const ServeQueue& q, ServeView&
       uint64_t w, id;
       m.add_load(q.claim + (size_t)s * (kServeLine / 2), ident, w, id);
       if ((id >> 32) != (w >> 32)) id = m.load(ident);
-      if ((w >> 32) != (e >> 32)) v.fresh = false;   // a job published after the list was seen
       const uint32_t limit = (id >> 32) == (w >> 32) ? (uint32_t)id : 0u;
       if ((uint32_t)w >= limit) {
         v.spent |= 1ull << at;
         continue;
       }
+      const uint32_t gen = (uint32_t)(w >> 32);
+      v.acquire = v.cold || (int32_t)(gen - v.acquired) > 0;
+      if (v.acquire) v.acquired = (int32_t)(v.version - gen) > 0 ? v.version : gen;
+      v.cold = false;
       m.claimed(q);
       // the job's last item: tell the host, which then lists the job no more
       if ((uint32_t)w + 1 == limit) m.store(q.host_claimed + (size_t)s * (kServeLine / 2) + 1, w >> 32);
@@ -131,7 +143,7 @@ __host__ __device__ inline void serve_publish(M& m, const ServeUpdate* u, int n_
   for (int k = tid; k < n_jobs * kWords; k += nt)
     m.store(reinterpret_cast<uint64_t*>(q.slots + u->slot[k / kWords]) + k % kWords, src[k]);
   const int slot = tid < n_jobs ? u->slot[tid] : 0;
-  const uint64_t word = tid < n_jobs ? u->job[tid].ident >> 32 << 32 : 0;
+  const uint64_t word = (uint64_t)version << 32;
   const uint64_t entry = tid < n_active ? u->active[tid] : 0;
   if (tid < n_jobs) m.exchange(q.done + (size_t)slot * kServeLine, 0u);
   m.settle();

@@ -1748,7 +1748,7 @@ __global__ __launch_bounds__(256, 2) void xeng_serve_kernel(ServeQueue q) {
   if (threadIdx.x == 0)   // a new grid counts as activity: it lingers idle_ticks before it may close
     __hip_atomic_fetch_max(q.last_claim, (uint64_t)wall_clock64(), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   ServeMemory mem;
-  ServeView view{blockIdx.x, 1, 0, 0, false};
+  ServeView view{blockIdx.x, 1, 0, 0, 0, true, false};
   for (;;) {
     __syncthreads();   // the previous tile's LDS reads are done
     if (threadIdx.x < 64) {
@@ -1756,12 +1756,7 @@ __global__ __launch_bounds__(256, 2) void xeng_serve_kernel(ServeQueue q) {
       uint64_t word = 0;
       if (threadIdx.x == 0) slot = serve_claim(mem, q, view, &word);
       slot = __builtin_amdgcn_readfirstlane(slot);
-      // Samples may have been written since the grid started, into memory that
-      // this CU or XCD has cached: drop what it holds, once for each list seen.
-      if (!__builtin_amdgcn_readfirstlane((int)view.fresh)) {
-        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "");
-        view.fresh = true;
-      }
+      if (slot >= 0 && __builtin_amdgcn_readfirstlane((int)view.acquire)) __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "");
       if (slot >= 0 && threadIdx.x < kWords)
         reinterpret_cast<uint64_t*>(&sc->job)[threadIdx.x] =
             sys_load64(reinterpret_cast<const uint64_t*>(q.slots + slot) + threadIdx.x);

@@ -10,7 +10,9 @@
 //
 // Checked in every execution: a claimed item exists, belongs to the job whose
 // record the slot holds, and is claimed once; the host is told "last item" for
-// the last one only.
+// the last one only; the workgroup that claims an item sees the samples of its
+// job (a word that stands for them is stored ahead of the update, and an
+// acquire is a load of it).
 // Usage: serve_model SCENARIO; exit status 0 and the number of executions, or 1
 // and the first faulty one.
 #include <ucontext.h>
@@ -31,6 +33,7 @@ using namespace corr;
 namespace {
 
 constexpr int kSlotsUsed = 4;
+constexpr uint32_t kVersion = 7;   // of the list that the workgroups have seen; the update is the next one
 
 // ------------------------------------------------------------------ scenario
 struct JobSpec {
@@ -54,6 +57,7 @@ struct Memory {
   uint64_t active[1 + 2 * kServeSlots];
   uint64_t host[kServeSlots * kServeLine / 2];
   uint64_t last_claim;
+  uint64_t samples;              // number of the latest update whose jobs' samples are in memory
   uint32_t closing, host_closing;
 } mem;
 
@@ -118,7 +122,7 @@ bool watched(const uint64_t* p) {
   if (p >= mem.claim && p < mem.claim + kServeSlots * kServeLine / 2) return true;
   for (int s = 0; s < kSlotsUsed; ++s)
     if (p == &mem.slots[s].ident) return true;
-  return false;
+  return p == &mem.samples;
 }
 
 void post(Kind k, const uint64_t* p, uint64_t value, uint64_t* out) {
@@ -229,11 +233,14 @@ std::vector<ServeView> views;
 void claimer(int c) {
   ModelMemory m;
   const ServeQueue q = queue();
+  uint64_t seen = kVersion;
   for (int k = 0; k < scene->calls; ++k) {
     uint64_t w = 0;
     const int slot = serve_claim(m, q, views[c], &w);
-    views[c].fresh = true;
-    if (slot >= 0) check_claim(slot, w);
+    if (slot < 0) continue;
+    check_claim(slot, w);
+    if (views[c].acquire) seen = m.load(&mem.samples);
+    if (seen < (w >> 32)) fail("an item is multiplied without its job's samples having been acquired");
   }
   wait_all();
 }
@@ -245,7 +252,7 @@ void setup(std::vector<Actor>& as) {
   items_of.clear();
   trace.clear();
   fault.clear();
-  constexpr uint32_t kVersion = 7;
+  mem.samples = kVersion;
   int n = 0;
   std::map<int, JobSpec> jobs;
   for (const JobSpec& j : scene->before) jobs[j.slot] = j;
@@ -256,7 +263,7 @@ void setup(std::vector<Actor>& as) {
     for (const JobSpec& l : scene->live) is_live = is_live || l.slot == j.slot;
     mem.slots[j.slot] = record(j);
     mem.claim[j.slot * (kServeLine / 2)] = (uint64_t)j.gen << 32 | (uint64_t)(is_live ? 0 : j.n_items);
-    mem.active[1 + n++] = serve_entry(j.slot, j.gen);
+    mem.active[1 + n++] = (uint64_t)j.slot;
     items_of[{j.slot, j.gen}] = j.n_items;
   }
   mem.active[0] = (uint64_t)kVersion << 32 | (uint64_t)n;
@@ -267,8 +274,8 @@ void setup(std::vector<Actor>& as) {
     items_of[{j.slot, j.gen}] = j.n_items;
     jobs[j.slot] = j;
   }
-  for (size_t k = 0; k < scene->list.size(); ++k) update.active[k] = serve_entry(scene->list[k], jobs[scene->list[k]].gen);
-  views.assign(scene->claimers, ServeView{0, (uint32_t)n, kVersion, 0, true});
+  for (size_t k = 0; k < scene->list.size(); ++k) update.active[k] = (uint64_t)scene->list[k];
+  views.assign(scene->claimers, ServeView{0, (uint32_t)n, kVersion, 0, kVersion, false, false});
   for (int c = 0; c < scene->claimers; ++c) views[c].turn = (uint32_t)c;
 
   const int nt = (int)std::max(scene->next.size(), scene->list.size()) + 1;
@@ -278,7 +285,9 @@ void setup(std::vector<Actor>& as) {
     as[t].publisher = true;
     as[t].body = [t, nt] {
       ModelMemory m;
-      serve_publish(m, &update, (int)scene->next.size(), (int)scene->list.size(), 8, queue(), t, nt);
+      if (t == 0) m.store(&mem.samples, kVersion + 1);
+      m.settle();   // the samples are there before the update's kernel starts
+      serve_publish(m, &update, (int)scene->next.size(), (int)scene->list.size(), kVersion + 1, queue(), t, nt);
       wait_all();
     };
   }
@@ -361,7 +370,7 @@ std::string name_of(const uint64_t* p) {
   } else if (p >= mem.claim && p < mem.claim + kServeSlots * kServeLine / 2) {
     std::snprintf(s, sizeof(s), "claim[%d]", (int)((p - mem.claim) / (kServeLine / 2)));
   } else {
-    std::snprintf(s, sizeof(s), "identity");
+    std::snprintf(s, sizeof(s), p == &mem.samples ? "samples" : "identity");
   }
   return s;
 }
@@ -407,14 +416,14 @@ bool explore(std::vector<Op> sleep) {
 const std::map<std::string, Scenario>& scenarios() {
   static const std::map<std::string, Scenario> all = {
       // a slot's next job in the same place of the list, with fewer, more and as many items
-      {"shrinking", {{{3, 5, 4}}, {}, {{3, 6, 1}}, {3}, 2, 2}},
-      {"growing", {{{3, 5, 1}}, {}, {{3, 6, 3}}, {3}, 2, 2}},
-      {"equal", {{{3, 5, 2}}, {}, {{3, 6, 2}}, {3}, 2, 2}},
-      // the place goes to another slot, whose generation is the former one's
-      {"moved", {{{1, 5, 4}}, {}, {{2, 5, 2}}, {2}, 2, 2}},
+      {"shrinking", {{{3, 5, 4}}, {}, {{3, 8, 1}}, {3}, 2, 2}},
+      {"growing", {{{3, 5, 1}}, {}, {{3, 8, 3}}, {3}, 2, 2}},
+      {"equal", {{{3, 5, 2}}, {}, {{3, 8, 2}}, {3}, 2, 2}},
+      // the place goes to another slot
+      {"moved", {{{1, 5, 4}}, {}, {{2, 8, 2}}, {2}, 2, 2}},
       // the list grows in front of a job that has unclaimed items, and shrinks
-      {"longer", {{{1, 4, 3}}, {{3, 5, 2}}, {{2, 6, 1}}, {2, 3}, 1, 4}},
-      {"shorter", {{{1, 4, 3}, {2, 6, 4}}, {}, {{2, 7, 2}}, {2}, 1, 4}},
+      {"longer", {{{1, 4, 3}}, {{3, 5, 2}}, {{2, 8, 1}}, {2, 3}, 1, 4}},
+      {"shorter", {{{1, 4, 3}, {2, 6, 4}}, {}, {{2, 8, 2}}, {2}, 1, 4}},
   };
   return all;
 }
