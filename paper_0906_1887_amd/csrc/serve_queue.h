@@ -77,6 +77,12 @@ struct ServeView {
 // a word of its own, an entry loaded while the slot's next job was listed could
 // give that job its predecessor's count.)
 //
+// A list's entries are in memory before its head, so an entry that is loaded
+// once the head has shown a list is that list's or a later one's: what is noted
+// of its place holds for the list, or until the later head is seen.  The entry
+// that came with a new head may be older, and is loaded again.  (A place noted
+// as spent by it hid the new list's job there from the workgroup.)
+//
 // Samples may have been written since the grid started, into memory that this
 // CU or XCD has cached.  What was published by an update was written before it,
 // so one acquire after the list's head or a claim word has shown update u makes
@@ -93,11 +99,12 @@ __host__ __device__ inline int serve_claim(M& m, const ServeQueue& q, ServeView&
     m.load2(q.active, q.active + 1 + at, head, e);
     if (closing >= q.gen) return -1;
     const uint32_t n = (uint32_t)head < (uint32_t)q.n_slots ? (uint32_t)head : (uint32_t)q.n_slots;
-    bool fetched = n == v.n;
-    if ((uint32_t)(head >> 32) != v.version || !fetched) {
+    bool fetched = true;
+    if ((uint32_t)(head >> 32) != v.version) {
       v.version = (uint32_t)(head >> 32);
       v.spent = 0;
       if (n > 0) v.n = n;
+      fetched = false;
     }
     for (uint32_t a = 0; a < n; ++a, fetched = false) {
       at = v.turn++ % n;
@@ -129,12 +136,13 @@ __host__ __device__ inline int serve_claim(M& m, const ServeQueue& q, ServeView&
   return -1;
 }
 
-// One of nt threads (at least kServeSlots) of an update: the jobs' records and
-// done counts, then their slots' claim words (no item of a job is claimed
-// before its claim word is set, so its record is seen first), then the list of
-// active slots.  The slots' former jobs are complete.  settle() returns once
-// every store of every thread before it has reached memory.  The words that
-// later steps store are read from host memory ahead of the first wait.
+// One of nt threads (at least one more than kServeSlots) of an update: the
+// jobs' records and done counts, then their slots' claim words (no item of a
+// job is claimed before its claim word is set, so its record is seen first),
+// then the list's entries, then its head.  The slots' former jobs are complete.
+// settle() returns once every store of every thread before it has reached
+// memory.  The words that later steps store are read from host memory ahead of
+// the first wait.
 template <class M>
 __host__ __device__ inline void serve_publish(M& m, const ServeUpdate* u, int n_jobs, int n_active, uint32_t version,
                                               const ServeQueue& q, int tid, int nt) {
@@ -150,6 +158,7 @@ __host__ __device__ inline void serve_publish(M& m, const ServeUpdate* u, int n_
   if (tid < n_jobs) m.exchange(q.claim + (size_t)slot * (kServeLine / 2), word);
   m.settle();
   if (tid < n_active) m.store(q.active + 1 + tid, entry);
+  m.settle();
   if (tid == nt - 1) m.store(q.active, (uint64_t)version << 32 | (uint64_t)n_active);
 }
 

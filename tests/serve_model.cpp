@@ -12,7 +12,8 @@
 // record the slot holds, and is claimed once; the host is told "last item" for
 // the last one only; the workgroup that claims an item sees the samples of its
 // job (a word that stands for them is stored ahead of the update, and an
-// acquire is a load of it).
+// acquire is a load of it); and, once the update has been applied, any one of
+// the workgroups would claim all that is left in one turn of the list.
 // Usage: serve_model SCENARIO; exit status 0 and the number of executions, or 1
 // and the first faulty one.
 #include <ucontext.h>
@@ -230,6 +231,25 @@ ServeUpdate update;
 const Scenario* scene;
 std::vector<ServeView> views;
 
+// All that is left goes to workgroup c, without another update.
+void check_rest(int c) {
+  const Memory saved = mem;
+  const Ledger claims = ledger;
+  ModelMemory m;
+  const ServeQueue q = queue();
+  ServeView v = views[c];
+  uint64_t w = 0;
+  for (int slot = serve_claim(m, q, v, &w); slot >= 0; slot = serve_claim(m, q, v, &w)) check_claim(slot, w);
+  for (const JobSpec& j : scene->live)
+    for (int k = 0; k < j.n_items; ++k)
+      if (!ledger.claims.count({j.slot, (uint64_t)j.gen << 32 | (uint64_t)k})) fail("a workgroup ignores a listed job");
+  for (const JobSpec& j : scene->next)
+    for (int k = 0; k < j.n_items; ++k)
+      if (!ledger.claims.count({j.slot, (uint64_t)j.gen << 32 | (uint64_t)k})) fail("a workgroup ignores a listed job");
+  mem = saved;
+  ledger = claims;
+}
+
 void claimer(int c) {
   ModelMemory m;
   const ServeQueue q = queue();
@@ -394,7 +414,8 @@ bool explore(std::vector<Op> sleep) {
   const std::vector<Op> en = enabled();
   if (en.empty()) {
     ++executions;
-    return true;
+    for (int c = 0; c < scene->claimers; ++c) check_rest(c);
+    return report();
   }
   auto same = [](const Op& a, const Op& b) { return a.actor == b.actor && a.seq == b.seq; };
   for (const Op& t : en) {
