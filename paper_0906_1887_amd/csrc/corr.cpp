@@ -277,9 +277,10 @@ void release_host_slot(corr_plan* p) {
   p->host_slot = -1;
 }
 
-// Device memory on the workspace's GPU, which the plan's kernels can write;
-// anything else (another GPU's memory, managed or host memory passed as
-// device memory) goes through the runtime's copy.
+// Device memory on the workspace's GPU, `bytes` of it within its allocation,
+// which the plan's kernels can write; anything else (another GPU's memory,
+// managed or host memory passed as device memory) goes through the runtime's
+// copy, which refuses a destination that is too small.
 int device_of(const void* ptr) {
   hipPointerAttribute_t at;
   if (hipPointerGetAttributes(&at, ptr) != hipSuccess) {
@@ -288,10 +289,18 @@ int device_of(const void* ptr) {
   }
   return at.type == hipMemoryTypeDevice && !at.isManaged ? at.device : -1;
 }
-bool kernel_writable(corr_plan* p, const void* dst) {
+bool kernel_writable(corr_plan* p, void* dst, size_t bytes) {
   if ((reinterpret_cast<uintptr_t>(dst) & 3) != 0) return false;
   if (p->device < 0) p->device = device_of(p->ws);
-  return p->device >= 0 && device_of(dst) == p->device;
+  if (p->device < 0 || device_of(dst) != p->device) return false;
+  hipDeviceptr_t base = nullptr;
+  size_t size = 0;
+  if (hipMemGetAddressRange(&base, &size, dst) != hipSuccess) {
+    (void)hipGetLastError();
+    return false;
+  }
+  const size_t at = (size_t)(static_cast<uint8_t*>(dst) - static_cast<uint8_t*>(base));
+  return at <= size && bytes <= size - at;
 }
 
 // Launch one X-engine pass over samples [n_ch][n_in][row_stride] (bytes per
@@ -863,7 +872,7 @@ corr_status corr_dump(corr_plan* p, int32_t what, void* dst, int32_t dst_is_devi
       // takes 20.9 us at 32 KB, 22.3 at 65 KB and 29.3 at 234 KB, through the
       // runtime's copy to pageable memory 30.3 (34 KB), 31.5 and 38.7.
       const bool staged = copy && !dst_is_device && slot && bytes <= kHostSlotBytes - kHostWord;
-      const bool direct = copy && dst_is_device && kernel_writable(p, dst);
+      const bool direct = copy && dst_is_device && kernel_writable(p, dst, bytes);
       corr::DumpCall d;
       std::memset(&d, 0, sizeof(d));
       d.is_int = c.engine == CORR_X_I8;
