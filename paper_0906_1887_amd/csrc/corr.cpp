@@ -230,7 +230,7 @@ hipError_t ensure_guards(corr_plan* p) {
 // guard check's result word, written by the dump's kernel, and after it room
 // for a small integration on its way to pageable host memory.  One 4 MB block
 // per process, allocated by the first dump that waits and kept; slots return
-// when their plan is destroyed (its dumps have been waited for).  A plan that
+// when their plan is destroyed (its dumps have been waited for, failed ones too).  A plan that
 // finds no slot reads the word back with a copy instead.
 constexpr int kHostSlots = 32;
 constexpr size_t kHostSlotBytes = 128 << 10;
@@ -889,8 +889,14 @@ corr_status corr_dump(corr_plan* p, int32_t what, void* dst, int32_t dst_is_devi
       d.ws = check ? p->ws : nullptr;
       d.guards = L.guards;
       d.bad = slot ? reinterpret_cast<uint32_t*>(page_dev) : static_cast<uint32_t*>(at(p, L.status));
+      // Whatever fails from here on, the kernel may still have to write to the
+      // slot: the call ends after it, or the slot goes to no other plan.
+      auto fail = [&](hipError_t err) {
+        if (slot && hipStreamSynchronize(p->stream) != hipSuccess) p->host_slot = -1;
+        return hip_fail(p, err);
+      };
       e = corr::launch_dump(d, p->stream);
-      if (e != hipSuccess) return hip_fail(p, e);
+      if (e != hipSuccess) return fail(e);
       if (do_fold) p->n_long += p->n_accum;
       if (copy && !direct && !staged)
         e = hipMemcpyAsync(dst, at(p, longrun ? L.longrun : L.acc), bytes,
@@ -899,14 +905,14 @@ corr_status corr_dump(corr_plan* p, int32_t what, void* dst, int32_t dst_is_devi
         e = (L.acc_bytes % 16 == 0 && (reinterpret_cast<uintptr_t>(dst) & 15) == 0)
                 ? corr::launch_fill_zero(dst, (int64_t)L.acc_bytes, p->stream)
                 : corr::launch_fill_zero_bytes(dst, (int64_t)L.acc_bytes, p->stream);
-      if (e != hipSuccess) return hip_fail(p, e);
+      if (e != hipSuccess) return fail(e);
       uint32_t bad = 0;
       if (check && !slot) {
         e = hipMemcpyAsync(&bad, at(p, L.status), sizeof(bad), hipMemcpyDeviceToHost, p->stream);
-        if (e != hipSuccess) return hip_fail(p, e);
+        if (e != hipSuccess) return fail(e);
       }
       e = hipStreamSynchronize(p->stream);
-      if (e != hipSuccess) return hip_fail(p, e);
+      if (e != hipSuccess) return fail(e);
       if (staged) std::memcpy(dst, page + kHostWord, bytes);
       if (check && slot) bad = *reinterpret_cast<volatile uint32_t*>(page);
       if (bad != 0) {

@@ -193,6 +193,12 @@ void device_free(void* p) {
   ranges().erase(static_cast<uint8_t*>(p));
   std::free(p);
 }
+size_t queued() {
+  std::lock_guard<std::recursive_mutex> lk(mu);
+  size_t n = null_stream.ops.size();
+  for (hipStream_t s : streams) n += s->ops.size();
+  return n;
+}
 size_t stores_outside() { return outside; }
 void queue_gate(hipStream_t s, const volatile bool* open) {
   push(s, [open] { return *open; });

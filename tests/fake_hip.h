@@ -12,6 +12,7 @@ namespace fake {
 
 void* device_alloc(size_t bytes);       // "device" memory, a range of its own
 void device_free(void* p);
+size_t queued();                        // operations that have not been executed
 size_t stores_outside();                // kernel stores that lay past their allocation
 // Queue an operation on a stream that ends only once `open` is set.
 void queue_gate(hipStream_t s, const volatile bool* open);

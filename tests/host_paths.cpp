@@ -3,11 +3,13 @@
 // Usage: host_paths SCENARIO; exit status 0 when its checks hold.
 #include <unistd.h>
 
+#include <chrono>
 #include <cstdio>
 #include <cstdlib>
 #include <cstring>
 #include <map>
 #include <string>
+#include <thread>
 
 #include "corr.h"
 #include "fake_hip.h"
@@ -65,8 +67,25 @@ void dump_range() {
   }
 }
 
+// A plan whose dump failed while its check was still queued: the pinned page
+// that the check will write to goes to no other plan before that.
+void dump_failed_in_flight() {
+  Plan a(config(9, 5));
+  void* small = fake::device_alloc(16);
+  fake::close_streams(true);
+  std::thread late([] {   // the GPU gets on only later
+    std::this_thread::sleep_for(std::chrono::milliseconds(200));
+    fake::close_streams(false);
+  });
+  CHECK(corr_dump(a.plan, CORR_DUMP_INTEG, small, 1, nullptr, nullptr) == CORR_E_HIP);
+  CHECK(corr_destroy(a.plan) == CORR_OK);
+  CHECK(fake::queued() == 0);
+  late.join();
+}
+
 const std::map<std::string, void (*)()> kScenarios = {
     {"dump_range", dump_range},
+    {"dump_failed_in_flight", dump_failed_in_flight},
 };
 
 }  // namespace

@@ -40,3 +40,7 @@ def run(exe, scenario):
 
 def test_dump_refuses_a_destination_that_is_too_small(exe):
     run(exe, "dump_range")
+
+
+def test_dump_that_fails_waits_for_what_it_queued(exe):
+    run(exe, "dump_failed_in_flight")
