@@ -91,7 +91,7 @@ struct Job {
   corr::ServeJob sj{};                 // its pass, as published
   bool claimed_all = false;            // the device has claimed every item
   uint32_t flag_value = 0;
-  uint32_t gen = 0;                    // the update that published it
+  uint32_t gen = 0;                    // the update that published it (0: none yet)
   corr_plan* plan = nullptr;
   int stream = -1;
   int64_t n_out = 0;
@@ -253,13 +253,21 @@ void on_done(void* arg) {
   o->callbacks.fetch_sub(1);
 }
 
+// Whether the next staging entry's former update has been applied.  Updates
+// queue up behind the fills on the control stream, for as long as those take;
+// the jobs of the batch wait for an entry, the scheduler (and whoever waits for
+// its lock) does not.
+bool stage_free(corr_sched* s) {
+  const int k = s->stage_next;
+  return !s->stage_used[k] || hipEventQuery(s->stage_ev[k]) != hipErrorNotReady;
+}
+
 // Publish the jobs of the batch and the list of slots holding jobs with
-// unclaimed items, through a pinned staging entry whose previous update has
-// been applied, by one kernel on the control stream (lock held).
+// unclaimed items, through the next staging entry (stage_free), by one kernel on
+// the control stream (lock held).
 hipError_t publish(corr_sched* s) {
   const int k = s->stage_next;
   s->stage_next = (k + 1) % kStage;
-  if (s->stage_used[k]) hipEventSynchronize(s->stage_ev[k]);
   s->stage_used[k] = true;
   static_assert(sizeof(corr::ServeUpdate) <= kStageBytes, "an update fits its staging entry");
   corr::ServeUpdate& u = *reinterpret_cast<corr::ServeUpdate*>(s->stage + (size_t)k * kStageBytes);
@@ -431,7 +439,7 @@ void retire_job(corr_sched* s, Job* j) {
 void collect_queue(corr_sched* s) {
   for (Job* j : s->running) {
     if (!j->queued_path || j->state.load() != kRunning) continue;
-    if (!j->claimed_all) {
+    if (j->gen != 0 && !j->claimed_all) {   // published
       const uint64_t c = __atomic_load_n(reinterpret_cast<const uint64_t*>(s->flags) +
                                              (size_t)j->slot * (corr::kServeLine / 2) + 1,
                                          __ATOMIC_ACQUIRE);
@@ -526,7 +534,7 @@ void worker_loop(corr_sched* s) {
         break;
       }
     }
-    if (!s->batch.empty()) {
+    if (!s->batch.empty() && stage_free(s)) {
       if (publish(s) != hipSuccess) {
         hipStreamSynchronize(s->s_ctl);
         for (Job* j : s->batch) fail_queued(s, j, CORR_E_HIP);

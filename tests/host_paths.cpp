@@ -83,9 +83,84 @@ void dump_failed_in_flight() {
   late.join();
 }
 
+// ---------------------------------------------------------------- scheduler
+// A job's fill ends once its gate is open.
+struct Gate {
+  volatile bool open = true;
+};
+void fill(void* user, uint64_t, void*, int64_t, int64_t, int64_t, int64_t, void* stream) {
+  fake::queue_gate(static_cast<hipStream_t>(stream), &static_cast<Gate*>(user)->open);
+}
+
+struct Serving {
+  corr_sched* s = nullptr;
+  size_t room = 0;   // arena bytes for jobs
+  explicit Serving(size_t arena) {
+    CHECK(corr_sched_create(fake::device_alloc(arena), arena, 1, &s) == CORR_OK);
+    int64_t st[8];
+    CHECK(corr_sched_stats(s, st) == CORR_OK);
+    room = (size_t)st[7];
+  }
+  uint64_t submit(int n_ch, int64_t n_samples, Gate* g) {
+    corr_job_desc d;
+    std::memset(&d, 0, sizeof(d));
+    d.n_inputs = 16;
+    d.n_channels = n_ch;
+    d.n_samples = n_samples;
+    d.max_abs = 7;
+    d.fill = fill;
+    d.fill_user = g;
+    d.dst = fake::device_alloc((size_t)n_ch * 136 * 8);
+    d.dst_is_device = 1;
+    uint64_t id = 0;
+    CHECK(corr_sched_submit(s, &d, corr_sched_now(), &id) == CORR_OK);
+    return id;
+  }
+  void until_admitted(int64_t n) {
+    int64_t st[8] = {};
+    while (corr_sched_stats(s, st) == CORR_OK && st[1] < n) std::this_thread::sleep_for(std::chrono::milliseconds(1));
+  }
+  bool done(uint64_t id, double seconds) {
+    const double t0 = corr_sched_now();
+    do {
+      const corr_status st = corr_sched_poll(s, id, nullptr, nullptr, nullptr, nullptr);
+      if (st != CORR_E_BUSY) return st == CORR_OK;
+      std::this_thread::sleep_for(std::chrono::milliseconds(1));
+    } while (corr_sched_now() - t0 < seconds);
+    return false;
+  }
+};
+
+// The process ends if what follows takes longer: a call that blocks would do so for good.
+void limit(int seconds, const char* what) {
+  std::thread([=] {
+    std::this_thread::sleep_for(std::chrono::seconds(seconds));
+    std::fprintf(stderr, "still waiting: %s\n", what);
+    _exit(1);
+  }).detach();
+}
+
+// Jobs whose fills take their time on the GPU, one update each: submission and
+// the other calls go on while all 64 slots wait.
+void submit_never_blocks() {
+  Serving v(64 << 20);
+  Gate g;
+  g.open = false;
+  uint64_t id[64];
+  limit(20, "a call while the fills of admitted jobs are running");
+  for (int k = 0; k < 64; ++k) {
+    id[k] = v.submit(2, 64, &g);
+    v.until_admitted(k + 1);
+  }
+  g.open = true;
+  for (uint64_t j : id) CHECK(v.done(j, 15.0));
+  CHECK(corr_sched_destroy(v.s) == CORR_OK);
+}
+
 const std::map<std::string, void (*)()> kScenarios = {
     {"dump_range", dump_range},
     {"dump_failed_in_flight", dump_failed_in_flight},
+    {"submit_never_blocks", submit_never_blocks},
 };
 
 }  // namespace

@@ -44,3 +44,7 @@ def test_dump_refuses_a_destination_that_is_too_small(exe):
 
 def test_dump_that_fails_waits_for_what_it_queued(exe):
     run(exe, "dump_failed_in_flight")
+
+
+def test_submission_goes_on_while_fills_run(exe):
+    run(exe, "submit_never_blocks")
