@@ -312,6 +312,16 @@ void fail_queued(corr_sched* s, Job* j, corr_status rc) {
   j->state.store(kDone);
 }
 
+// Publish what the batch holds if a staging entry is free (lock held).
+void publish_batch(corr_sched* s) {
+  if (s->batch.empty() || !stage_free(s)) return;
+  if (publish(s) != hipSuccess) {
+    hipStreamSynchronize(s->s_ctl);
+    for (Job* j : s->batch) fail_queued(s, j, CORR_E_HIP);
+  }
+  s->batch.clear();
+}
+
 // Admit one job on the device queue: queue its fill and add it to the batch
 // that the next update publishes (lock held).
 void launch_queued(corr_sched* s, Job* j) {
@@ -526,6 +536,7 @@ void worker_loop(corr_sched* s) {
         j->off = off;
         s->pending.erase(s->pending.begin() + k);
         if (j->queued_path) {
+          if (j->d.fill) publish_batch(s);   // so that its fill holds up no job but its own
           launch_queued(s, j);
         } else {
           launch_plan_job(s, j);
@@ -534,13 +545,7 @@ void worker_loop(corr_sched* s) {
         break;
       }
     }
-    if (!s->batch.empty() && stage_free(s)) {
-      if (publish(s) != hipSuccess) {
-        hipStreamSynchronize(s->s_ctl);
-        for (Job* j : s->batch) fail_queued(s, j, CORR_E_HIP);
-      }
-      s->batch.clear();
-    }
+    publish_batch(s);
     launch_grids(s);
     if (s->stop && s->pending.empty() && s->running.empty()) break;
     bool busy = s->work_since_launch || s->grid_alive[0] || s->grid_alive[1];

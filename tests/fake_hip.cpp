@@ -8,9 +8,11 @@
 #include <deque>
 #include <functional>
 #include <map>
+#include <memory>
 #include <mutex>
 #include <string>
 #include <thread>
+#include <vector>
 
 #include "launch.h"
 
@@ -91,7 +93,9 @@ bool fits(const void* p, size_t bytes) {
 }
 
 // ----------------------------------------------------------------- kernels
-// The queue in host memory, and a serving "grid" that ends once it finds nothing.
+// The queue in host memory, and a serving "grid" of one workgroup that closes
+// once it has found nothing for kIdle.
+constexpr std::chrono::milliseconds kIdle(100);
 struct HostMemory {
   uint64_t load(const uint64_t* p) { return *p; }
   uint32_t load_agent(const uint32_t* p) { return *p; }
@@ -110,23 +114,29 @@ struct HostMemory {
   }
   void settle() {}
   void claimed(const corr::ServeQueue&) {}
-  bool idle(const corr::ServeQueue& q) {
+  bool idle(const corr::ServeQueue&) { return true; }
+};
+
+struct Grid {
+  corr::ServeQueue q;
+  corr::ServeView v{0, 1, 0, 0, 0, true, false};
+  std::chrono::steady_clock::time_point last = std::chrono::steady_clock::now();
+
+  bool run() {
+    HostMemory m;
+    uint64_t w = 0;
+    for (int slot = corr::serve_claim(m, q, v, &w); slot >= 0; slot = corr::serve_claim(m, q, v, &w)) {
+      const corr::ServeJob& j = q.slots[slot];
+      if (++q.done[(size_t)slot * corr::kServeLine] == (uint32_t)j.x.n_items)
+        __atomic_store_n(j.flag, j.flag_value, __ATOMIC_RELEASE);
+      last = std::chrono::steady_clock::now();
+    }
+    if (std::chrono::steady_clock::now() - last < kIdle) return false;
     *q.closing = q.gen;
     __atomic_store_n(q.host_closing, q.gen, __ATOMIC_RELEASE);
     return true;
   }
 };
-
-void serve(corr::ServeQueue q) {
-  HostMemory m;
-  corr::ServeView v{0, 1, 0, 0, 0, true, false};
-  uint64_t w = 0;
-  for (int slot = corr::serve_claim(m, q, v, &w); slot >= 0; slot = corr::serve_claim(m, q, v, &w)) {
-    const corr::ServeJob& j = q.slots[slot];
-    if (++q.done[(size_t)slot * corr::kServeLine] == (uint32_t)j.x.n_items)
-      __atomic_store_n(j.flag, j.flag_value, __ATOMIC_RELEASE);
-  }
-}
 
 template <typename T>
 T arg(void** args, int k) {
@@ -147,11 +157,9 @@ std::function<bool()> kernel(const std::string& name, void** args) {
     };
   }
   if (has("xeng_serve_kernel")) {
-    const corr::ServeQueue q = arg<corr::ServeQueue>(args, 0);
-    return [=] {
-      serve(q);
-      return true;
-    };
+    auto g = std::make_shared<Grid>();
+    g->q = arg<corr::ServeQueue>(args, 0);
+    return [=] { return g->run(); };
   }
   if (has("fill_zero_kernel")) {
     void* p = arg<void*>(args, 0);

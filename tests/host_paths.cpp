@@ -157,10 +157,30 @@ void submit_never_blocks() {
   CHECK(corr_sched_destroy(v.s) == CORR_OK);
 }
 
+// Two jobs admitted together: the first one runs while the second's fill does.
+void fills_overlap() {
+  Serving v(2 << 20);
+  Gate first, quick, slow;
+  first.open = slow.open = false;
+  limit(30, "a job's turn");
+  const uint64_t all = v.submit(8, (int64_t)(v.room / 2048 * 8), &first);   // 256 bytes a sample: the whole arena
+  v.until_admitted(1);
+  const uint64_t a = v.submit(2, 64, &quick), b = v.submit(2, 64, &slow);
+  int64_t st[8] = {};
+  CHECK(corr_sched_stats(v.s, st) == CORR_OK && st[1] == 1 && st[4] == 2);
+  first.open = true;
+  CHECK(v.done(all, 5.0));
+  CHECK(v.done(a, 5.0));
+  slow.open = true;
+  CHECK(v.done(b, 5.0));
+  CHECK(corr_sched_destroy(v.s) == CORR_OK);
+}
+
 const std::map<std::string, void (*)()> kScenarios = {
     {"dump_range", dump_range},
     {"dump_failed_in_flight", dump_failed_in_flight},
     {"submit_never_blocks", submit_never_blocks},
+    {"fills_overlap", fills_overlap},
 };
 
 }  // namespace

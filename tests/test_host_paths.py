@@ -48,3 +48,7 @@ def test_dump_that_fails_waits_for_what_it_queued(exe):
 
 def test_submission_goes_on_while_fills_run(exe):
     run(exe, "submit_never_blocks")
+
+
+def test_a_job_runs_while_the_next_one_is_filled(exe):
+    run(exe, "fills_overlap")
