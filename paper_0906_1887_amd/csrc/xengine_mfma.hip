@@ -1810,11 +1810,17 @@ __global__ __launch_bounds__(256) void xeng_publish_kernel(const ServeUpdate* __
   serve_publish(mem, u, n_jobs, n_active, version, q, (int)threadIdx.x, 256);
 }
 
+// The launch's own status, here and in launch_xeng_serve: hipGetLastError may
+// give an error that a job's fill left behind in the scheduler's thread, and an
+// update that was queued must not be taken for one that was not (its jobs would
+// be failed, and their slots and arena regions given away, with the update still
+// to come).
 hipError_t launch_xeng_publish(const ServeUpdate* u, int n_jobs, int n_active, uint32_t version, const ServeQueue& q,
                                hipStream_t s) {
   if (n_jobs > kServeSlots || n_active > kServeSlots) return hipErrorInvalidValue;
-  hipLaunchKernelGGL(xeng_publish_kernel, dim3(1), dim3(256), 0, s, u, n_jobs, n_active, version, q);
-  return hipGetLastError();
+  ServeQueue queue = q;
+  void* args[] = {&u, &n_jobs, &n_active, &version, &queue};
+  return hipLaunchKernel(reinterpret_cast<const void*>(&xeng_publish_kernel), dim3(1), dim3(256), args, 0, s);
 }
 
 hipError_t launch_xeng_mfma(const XArgs& a, int elem, int bt, hipStream_t s) {
@@ -1851,8 +1857,9 @@ hipError_t launch_xeng_mfma(const XArgs& a, int elem, int bt, hipStream_t s) {
 
 hipError_t launch_xeng_serve(const ServeQueue& q, int grid, hipStream_t s) {
   if (grid <= 0) return hipSuccess;
-  hipLaunchKernelGGL(xeng_serve_kernel, dim3((unsigned)grid), dim3(256), 0, s, q);
-  return hipGetLastError();
+  ServeQueue queue = q;
+  void* args[] = {&queue};
+  return hipLaunchKernel(reinterpret_cast<const void*>(&xeng_serve_kernel), dim3((unsigned)grid), dim3(256), args, 0, s);
 }
 
 int serve_blocks_per_cu() {

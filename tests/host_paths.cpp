@@ -101,14 +101,14 @@ struct Serving {
     CHECK(corr_sched_stats(s, st) == CORR_OK);
     room = (size_t)st[7];
   }
-  uint64_t submit(int n_ch, int64_t n_samples, Gate* g) {
+  uint64_t submit(int n_ch, int64_t n_samples, Gate* g, corr_fill_fn f = fill) {
     corr_job_desc d;
     std::memset(&d, 0, sizeof(d));
     d.n_inputs = 16;
     d.n_channels = n_ch;
     d.n_samples = n_samples;
     d.max_abs = 7;
-    d.fill = fill;
+    d.fill = f;
     d.fill_user = g;
     d.dst = fake::device_alloc((size_t)n_ch * 136 * 8);
     d.dst_is_device = 1;
@@ -130,6 +130,11 @@ struct Serving {
     return false;
   }
 };
+
+// A fill whose own calls left an error behind that it has dealt with.
+void fill_with_error(void*, uint64_t, void*, int64_t, int64_t, int64_t, int64_t, void*) {
+  fake::set_last_error(hipErrorInvalidValue);
+}
 
 // The process ends if what follows takes longer: a call that blocks would do so for good.
 void limit(int seconds, const char* what) {
@@ -176,11 +181,20 @@ void fills_overlap() {
   CHECK(corr_sched_destroy(v.s) == CORR_OK);
 }
 
+// An update that was queued is not taken for one that was not.
+void error_of_a_fill() {
+  Serving v(2 << 20);
+  limit(30, "a job's turn");
+  for (int k = 0; k < 3; ++k) CHECK(v.done(v.submit(2, 64, nullptr, fill_with_error), 5.0));
+  CHECK(corr_sched_destroy(v.s) == CORR_OK);
+}
+
 const std::map<std::string, void (*)()> kScenarios = {
     {"dump_range", dump_range},
     {"dump_failed_in_flight", dump_failed_in_flight},
     {"submit_never_blocks", submit_never_blocks},
     {"fills_overlap", fills_overlap},
+    {"error_of_a_fill", error_of_a_fill},
 };
 
 }  // namespace

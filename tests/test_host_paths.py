@@ -52,3 +52,7 @@ def test_submission_goes_on_while_fills_run(exe):
 
 def test_a_job_runs_while_the_next_one_is_filled(exe):
     run(exe, "fills_overlap")
+
+
+def test_an_error_left_by_a_fill_fails_no_job(exe):
+    run(exe, "error_of_a_fill")
