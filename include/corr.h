@@ -161,7 +161,11 @@ typedef struct {
                                  fft_size is 0                               */
 } corr_config;
 
-/* Bytes of device workspace a plan needs for `cfg`.  Host only.  The
+/* Bytes of device workspace a plan needs for `cfg`.  Host only.  It depends on
+ * the library's version, so ask it at run time: plain FP32 plans of small
+ * arrays hold up to 16 K-split partials of the accumulator's size, within 64
+ * MiB or what 1024 work items need (64 inputs x 128 channels: 36 MB in all,
+ * 19 MB before it split that far; 32 x 600: 38 and 8).  The
  * workspace holds the plan's regions, the integration accumulator first (at
  * offset 0, [n_channels][P][2]), each region padded to 256 bytes and followed
  * by a 256-byte guard band; its last 256 bytes are room for the guard check's
@@ -397,7 +401,7 @@ corr_status corr_dump_bytes(const corr_plan *plan, int32_t what, size_t *bytes);
  * stride) are correlated through a per-job plan on one of n_streams streams
  * instead.  A job whose footprint exceeds the whole arena is refused at
  * submission (CORR_E_WORKSPACE).  The scheduler allocates, besides its host
- * objects, about 200 KB of pinned host memory (completion words and the staging of
+ * objects, about 160 KB of pinned host memory (completion words and the staging of
  * queue updates); no device memory.
  * ------------------------------------------------------------------------ */
 typedef struct corr_sched corr_sched;

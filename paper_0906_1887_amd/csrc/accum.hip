@@ -131,7 +131,8 @@ __global__ void guard_fill_kernel(uint8_t* __restrict__ ws, GuardList gl) {
   reinterpret_cast<uint32_t*>(ws + gl.off[g])[w] = guard_word(g, w);
 }
 
-// One workgroup: count the band words that differ from the pattern.
+// One workgroup: compare the bands with the pattern; *bad is 0 if no word
+// differs, else the number of threads that saw one that does.
 __device__ __forceinline__ void guard_check(const uint8_t* __restrict__ ws, const GuardList& gl,
                                             uint32_t* __restrict__ bad) {
   constexpr int kWords = kGuardBytes / 4;

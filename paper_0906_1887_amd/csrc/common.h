@@ -58,6 +58,9 @@ __device__ __forceinline__ int64_t tri_index(int64_t i, int64_t j) { return i * 
 // behind the stores before it.  Later passes of an integration, 256 inputs x 512
 // channels x 512 samples: int8 124 -> 92 us, CI4 112 -> 79, FP16 283 -> 222; 355 x
 // 264 x 88: FP16 156 -> 115, FP8 247 -> 189; 1024 x 64 x 512 int8 259 -> 173.
+// Two engines still add one product at a time: the unaligned int8 one, whose
+// 128-row tile has no register to spare for it (22 spills), and the plain FP32
+// one, where it was not tried.
 constexpr uint32_t kNoProduct = 0xFFFFFFFFu;
 template <typename V, int N>
 __device__ __forceinline__ void add_products(V* __restrict__ out, const uint32_t (&off)[N], const V (&v)[N]) {
@@ -98,7 +101,9 @@ struct XArgs {
   int32_t n_ch;
   int32_t n_tiles;          // lower-triangle tiles per channel
   int32_t n_split;          // K splits
-  int32_t n_items;          // n_ch * n_tiles * n_split
+  int32_t n_items;          // workgroups with work: channels x tiles x splits for the engines that take one tile
+                            // each (item_decode); plain FP32 pairs diagonal tiles or takes several channels, and
+                            // the one-workgroup FP16 kernel has channels x splits
   int32_t per_xcd;          // ceil(n_items / 8)
   int32_t accumulate;       // 1: out += tile; 0: out = tile
   int32_t pad_;

@@ -43,8 +43,8 @@ hipError_t launch_guard_fill(uint8_t* ws, const GuardList& g, hipStream_t s);
 
 // What a dump queues, in one launch: the fold of the integration into the
 // long-run sum, the copy of either to dst, and the check of the guard bands
-// (the number of words that differ from the pattern goes to *bad, device or
-// mapped host memory).
+// (*bad, in device or mapped host memory, becomes 0 if every word has the
+// pattern, else the number of threads that saw one that has not).
 enum DumpMode {
   kDumpCheck = 0,      // guard check only
   kDumpCopy,           // dst = acc (n scalars of 4 bytes)

@@ -11,13 +11,14 @@
 // Device queue (the batched path).  An admitted job is published in a slot
 // of a job queue in the arena's head: its pass (sample and result pointers,
 // shape) and its number of work items, one per (channel, 128-row baseline
-// tile); the jobs admitted together are published by one small kernel, under
-// the number of that update.  A persistent serving grid (xeng_serve_kernel, as many
-// workgroups as the GPU holds at once but kCopyReserve) runs while published
-// work remains.  Its workgroups claim items round robin over the listed jobs,
-// so jobs that arrive while others run are taken up by the grid already on
-// the device and a small job is not queued behind a large one.  A job whose
-// items are all claimed leaves the list.  Once the queue
+// tile).  The jobs admitted together are published by one small kernel, under
+// the number of that update; a job whose samples a fill produces goes out
+// before the next fill is queued.  A persistent serving grid (xeng_serve_kernel,
+// as many workgroups as the GPU holds at once but kCopyReserve) runs while
+// published work remains.  Its workgroups claim items round robin over the
+// listed jobs, so jobs that arrive while others run are taken up by the grid
+// already on the device and a small job is not queued behind a large one.  A job
+// whose items are all claimed is not in the next update's list.  Once the queue
 // has been idle for kIdleUs the grid closes as a whole; the scheduler
 // launches a new full-size grid (alternating between two streams, so it can
 // start while the closing one finishes its last tiles) when work is published

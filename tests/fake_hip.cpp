@@ -208,8 +208,8 @@ size_t queued() {
   return n;
 }
 size_t stores_outside() { return outside; }
-void queue_gate(hipStream_t s, const volatile bool* open) {
-  push(s, [open] { return *open; });
+void queue_gate(hipStream_t s, const std::atomic<bool>* open) {
+  push(s, [open] { return open->load(); });
 }
 void close_streams(bool c) {
   std::lock_guard<std::recursive_mutex> lk(mu);

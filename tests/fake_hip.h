@@ -4,6 +4,7 @@
 // under test depend on; the others do nothing.
 #pragma once
 
+#include <atomic>
 #include <cstddef>
 
 #include <hip/hip_runtime_api.h>
@@ -15,7 +16,7 @@ void device_free(void* p);
 size_t queued();                        // operations that have not been executed
 size_t stores_outside();                // kernel stores that lay past their allocation
 // Queue an operation on a stream that ends only once `open` is set.
-void queue_gate(hipStream_t s, const volatile bool* open);
+void queue_gate(hipStream_t s, const std::atomic<bool>* open);
 void close_streams(bool closed);        // closed: nothing queued is executed
 void set_last_error(hipError_t e);      // what an earlier call of this thread left behind
 

@@ -3,6 +3,7 @@
 // Usage: host_paths SCENARIO; exit status 0 when its checks hold.
 #include <unistd.h>
 
+#include <atomic>
 #include <chrono>
 #include <cstdio>
 #include <cstdlib>
@@ -86,7 +87,7 @@ void dump_failed_in_flight() {
 // ---------------------------------------------------------------- scheduler
 // A job's fill ends once its gate is open.
 struct Gate {
-  volatile bool open = true;
+  std::atomic<bool> open{true};
 };
 void fill(void* user, uint64_t, void*, int64_t, int64_t, int64_t, int64_t, void* stream) {
   fake::queue_gate(static_cast<hipStream_t>(stream), &static_cast<Gate*>(user)->open);
@@ -166,7 +167,8 @@ void submit_never_blocks() {
 void fills_overlap() {
   Serving v(2 << 20);
   Gate first, quick, slow;
-  first.open = slow.open = false;
+  first.open = false;
+  slow.open = false;
   limit(30, "a job's turn");
   const uint64_t all = v.submit(8, (int64_t)(v.room / 2048 * 8), &first);   // 256 bytes a sample: the whole arena
   v.until_admitted(1);
