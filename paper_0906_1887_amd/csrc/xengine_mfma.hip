@@ -308,9 +308,10 @@ __device__ __forceinline__ void mfma_tile(const XArgs& a, int8_t* lds, int ch, i
   const int64_t out0 = (int64_t)split * a.out_split_stride + (int64_t)ch * a.n_products;
   // Few inputs: rows past the last one are passed by, and indexes come from one
   // multiplication.  The kernel on 2 inputs x 18 channels x 5112 samples FP16 in
-  // three chunks 6.84 -> 6.40 us, 10 x 21 x 116 5.96 -> 5.36, int8 1 x 3 x 328 4.96 -> 4.40.
-  // CI4 and FP8 gain less there and lose up to 5 % at 17 to 64 inputs.
-  constexpr bool kFew = EK == kElemI8 || EK == kElemF16;
+  // three chunks 6.84 -> 6.40 us, 10 x 21 x 116 5.96 -> 5.36.  Not for the others: CI4
+  // and FP8 lose up to 5 % at 17 to 64 inputs with it, int8 5 us of a pass of 64
+  // inputs x 128 channels x 10000 samples.
+  constexpr bool kFew = EK == kElemF16;
 #pragma unroll
   for (int m = 0; m < MB; ++m)
 #pragma unroll
