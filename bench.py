@@ -244,8 +244,8 @@ def serving(seconds: float, warm: float, rate: float, host: bool, seed: int = 5)
 # 128-row tiles).
 TRAFFIC_SOURCES = [os.path.join(ROOT, "paper_0906_1887_amd", "csrc", f)
                    for f in ("xengine_mfma.hip", "common.h")]
-TRAFFIC_SHA1 = "15e9c8991c5b64c76342e4d3346753a7083a14e8"
-TRAFFIC_BYTES = {"read": 2 * 23336464 * 1024, "write": 3341622 * 1024}
+TRAFFIC_SHA1 = "cf49428a786913a3200f2319dc0a8455b0a62319"
+TRAFFIC_BYTES = {"read": 2 * 23749144 * 1024, "write": 3342439 * 1024}
 
 
 def traffic_sources_sha1() -> str:
