@@ -95,7 +95,7 @@ bool fits(const void* p, size_t bytes) {
 // ----------------------------------------------------------------- kernels
 // The queue in host memory, and a serving "grid" of one workgroup that closes
 // once it has found nothing for kIdle.
-constexpr std::chrono::milliseconds kIdle(100);
+constexpr std::chrono::milliseconds kIdle(500);   // (a busy machine may hold a thread up)
 struct HostMemory {
   uint64_t load(const uint64_t* p) { return *p; }
   uint32_t load_agent(const uint32_t* p) { return *p; }
